@@ -270,6 +270,7 @@ struct HopArgs {
   double* cg_site;
   void* cg_x;
   const void* cg_p;
+  int chained;   // 1: the caller's next launch reads the output (nt_stores)
 };
 int launch_hop(qdwf_ctx* ctx, int prec, int layout, int dagger, const HopArgs& a,
                hipStream_t st, const HopShape* shape = nullptr);

@@ -372,6 +372,7 @@ int fill_mdagm(qdwf_ctx* ctx, int prec, const void* in, void* out, void* v, void
     a.hop_scale = -0.5;
     a.minv = ls16 ? 1 : 0;
     a.chi = (ls16 && !dag) ? 1 : 0;
+    a.chained = 1;
     if ((rc = fill_hop(ctx, prec, a, hk[2 * dag]))) return rc;
     GLoc& l = *lk[dag];
     l.in = te1;
@@ -395,6 +396,7 @@ int fill_mdagm(qdwf_ctx* ctx, int prec, const void* in, void* out, void* v, void
     b.alpha = al;
     b.beta = be;
     b.chi = dag ? 0 : 1;
+    b.chained = 1;
     if (cg) {
       b.cg = dag ? (cg->x ? 3 : 2) : 1;
       b.cg_r = cg->r;

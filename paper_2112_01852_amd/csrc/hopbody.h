@@ -52,6 +52,7 @@ struct HopK {
   double* cg_site;
   void* cg_x;          // cg = 3: inner solution, compute type
   const void* cg_p;    // cg = 3: search direction, storage type
+  int nt;              // store the output non-temporally (nt_stores)
 };
 
 // Target occupancy (waves per SIMD) the register allocator plans for: two for
@@ -361,9 +362,19 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
       int ss = s, lsb = Ls;
       riri_block(i, ss, lsb);
       uint2* pp = reinterpret_cast<uint2*>(out + i * lsb * 24 + (long)ss * 4);
+      uint2 w[6];
 #pragma unroll
       for (int c = 0; c < 6; ++c)
-        pp[c * lsb] = make_uint2(pk_f16(acc[4 * c], acc[4 * c + 1]), pk_f16(acc[4 * c + 2], acc[4 * c + 3]));
+        w[c] = make_uint2(pk_f16(acc[4 * c], acc[4 * c + 1]), pk_f16(acc[4 * c + 2], acc[4 * c + 3]));
+      if (k.nt) {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) put_word<true>(&pp[c * lsb], w[c]);
+      } else {
+#pragma unroll
+        for (int c = 0; c < 6; ++c) pp[c * lsb] = w[c];
+      }
+    } else if (k.nt) {
+      SiteIO<S, LAYOUT>::template store<true>(out, cbc, s, Ls, k.plane, acc);
     } else {
       SiteIO<S, LAYOUT>::store(out, cbc, s, Ls, k.plane, acc);
     }
@@ -416,7 +427,8 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
           ss += v * v;
         }
       }
-      SiteIO<RS, LAYOUT>::store(rr, cbc, s, Ls, k.plane, rv);
+      if (k.nt) SiteIO<RS, LAYOUT>::template store<true>(rr, cbc, s, Ls, k.plane, rv);
+      else SiteIO<RS, LAYOUT>::store(rr, cbc, s, Ls, k.plane, rv);
       if (k.cg == 3) {
         // the iteration's step at the same sites: x += alpha p
         T pv[24], xv[24];
@@ -475,6 +487,7 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
   k->cg_site = a.cg_site;
   k->cg_x = a.cg_x;
   k->cg_p = a.cg_p;
+  k->nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0);
   if (a.cg && (a.cg > 3 || !a.epi || a.npar != 1 || !a.cg_site ||
                (a.cg >= 2 && (!a.cg_r || !a.cg_alpha)) || (a.cg == 3 && (!a.cg_x || !a.cg_p))))
     return fail(QDWF_EINVAL, "fused CG step needs a one-parity hop with epilogue and its buffers");

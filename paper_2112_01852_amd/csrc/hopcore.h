@@ -16,6 +16,21 @@ __device__ inline int xcd_remap(int bid, int nb) {
   return (x < rem) ? x * (per + 1) + k : rem * (per + 1) + (x - rem) * per + k;
 }
 
+// Whether a launch that writes `bytes` stores them non-temporally. What the
+// hop gathers (each input spinor eight times, from blocks some planes apart)
+// is what L2 should hold, and a stored line only takes its room: with
+// non-temporal stores one-launch calls ran 3-13 % faster at every size tried
+// from 16 MB up (us: FP32 D 16^4 x 8 50.7 -> 44.0, D^dag 12^3x24 x 12 44.5 ->
+// 40.1, FP64 D 16^3x32 x 8 187 -> 178, FP32 D_eo 16^4 x 16 x 12 rhs 417 ->
+// 397). An output that the next launch of the same call reads (chained: the
+// stages of M_pc) is better left in the caches until it is too large for
+// them: M_pc^dag M_pc in FP16 at 16^4 x 16 (12 to 50 MB of right-hand sides)
+// 2-5 % slower, at 24^4 x 16 (127 MB) 464 -> 443, in FP64 (510 MB) 1568 ->
+// 1500.
+inline int nt_stores(size_t bytes, bool chained) {
+  return bytes >= ((size_t)(chained ? 64 : 16) << 20) ? 1 : 0;
+}
+
 // Link staging stride in LDS (reals per link): 16-byte aligned rows.
 template <class T> struct LinkStride { static constexpr int v = 20; };
 template <> struct LinkStride<double> { static constexpr int v = 18; };

@@ -44,6 +44,19 @@ __host__ __device__ inline long rrii_offset(long i, int s, int c, int Ls, long p
   return (long)((c & 1) * 12 + (c >> 1)) * plane + i * Ls + s;
 }
 
+// One aligned word (4, 8 or 16 bytes) to memory; NT: non-temporally, so that
+// the line does not displace data in L2 that is about to be read again.
+template <bool NT, class W> __device__ inline void put_word(W* p, W w) {
+  if constexpr (NT) {
+    typedef unsigned V __attribute__((ext_vector_type(sizeof(W) / 4)));
+    V v;
+    __builtin_memcpy(&v, &w, sizeof(W));
+    __builtin_nontemporal_store(v, reinterpret_cast<V*>(p));
+  } else {
+    *p = w;
+  }
+}
+
 template <class S, int LAYOUT> struct SiteIO;
 
 template <class S> struct SiteIO<S, QDWF_RRII> {
@@ -57,6 +70,7 @@ template <class S> struct SiteIO<S, QDWF_RRII> {
       v[2 * sc + 1] = Store<S>::to(f[(long)(12 + sc) * plane + j]);
     }
   }
+  template <bool NT = false>   // split planes keep plain stores
   __device__ static inline void store(S* __restrict__ f, long i, int s, int Ls, long plane,
                                       const T* v) {
     const long j = i * Ls + s;
@@ -82,14 +96,15 @@ template <> struct SiteIO<double, QDWF_RIRI> {
       v[4 * k + 3] = q1.y;
     }
   }
+  template <bool NT = false>
   __device__ static inline void store(double* __restrict__ f, long i, int s, int Ls, long,
                                       const double* v) {
     riri_block(i, s, Ls);
     double2* p = reinterpret_cast<double2*>(f + i * Ls * 24 + (long)s * 4);
 #pragma unroll
     for (int k = 0; k < 6; ++k) {
-      p[2 * k * Ls] = make_double2(v[4 * k], v[4 * k + 1]);
-      p[2 * k * Ls + 1] = make_double2(v[4 * k + 2], v[4 * k + 3]);
+      put_word<NT>(&p[2 * k * Ls], make_double2(v[4 * k], v[4 * k + 1]));
+      put_word<NT>(&p[2 * k * Ls + 1], make_double2(v[4 * k + 2], v[4 * k + 3]));
     }
   }
 };
@@ -108,13 +123,14 @@ template <> struct SiteIO<float, QDWF_RIRI> {
       v[4 * k + 3] = q.w;
     }
   }
+  template <bool NT = false>
   __device__ static inline void store(float* __restrict__ f, long i, int s, int Ls, long,
                                       const float* v) {
     riri_block(i, s, Ls);
     float4* p = reinterpret_cast<float4*>(f + i * Ls * 24 + (long)s * 4);
 #pragma unroll
     for (int k = 0; k < 6; ++k)
-      p[k * Ls] = make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]);
+      put_word<NT>(&p[k * Ls], make_float4(v[4 * k], v[4 * k + 1], v[4 * k + 2], v[4 * k + 3]));
   }
 };
 
@@ -133,6 +149,7 @@ template <class S> struct SiteIO16 {
       v[4 * k + 3] = Store<S>::to(bits((uint16_t)(q.y >> 16)));
     }
   }
+  template <bool NT = false>
   __device__ static inline void store(S* __restrict__ f, long i, int s, int Ls, long,
                                       const float* v) {
     riri_block(i, s, Ls);
@@ -143,7 +160,7 @@ template <class S> struct SiteIO16 {
                           ((uint32_t)raw(Store<S>::from(v[4 * k + 1])) << 16);
       const uint32_t w1 = (uint32_t)raw(Store<S>::from(v[4 * k + 2])) |
                           ((uint32_t)raw(Store<S>::from(v[4 * k + 3])) << 16);
-      p[k * Ls] = make_uint2(w0, w1);
+      put_word<NT>(&p[k * Ls], make_uint2(w0, w1));
     }
   }
   __device__ static inline S bits(uint16_t u);

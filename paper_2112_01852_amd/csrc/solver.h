@@ -62,13 +62,16 @@ Layout solver_layout(long n, int nrhs, int inner, bool grouped = false);
 
 int reduce_blocks(long n);
 int site_blocks(long nsite);
-// skip, skip_stride: per right-hand-side flags of the hops (HopArgs::skip)
+// skip, skip_stride: per right-hand-side flags of the hops (HopArgs::skip);
+// chained: the caller's next launch reads the result (HopArgs::chained)
 int apply_hop_parity(qdwf_ctx* ctx, int prec, int layout, int dagger, int out_par, void* out,
                      const void* in, const void* z, double scale, int nrhs, long rs,
-                     hipStream_t st, const int* skip = nullptr, int skip_stride = 0);
+                     hipStream_t st, const int* skip = nullptr, int skip_stride = 0,
+                     bool chained = false);
 int apply_mpc(qdwf_ctx* ctx, int prec, int layout, int dagger, void* out, const void* in,
               void* te1, void* te2, int nrhs, long rs, hipStream_t st,
-              const int* skip = nullptr, int skip_stride = 0, const CgFuse* cg = nullptr);
+              const int* skip = nullptr, int skip_stride = 0, const CgFuse* cg = nullptr,
+              bool chained = false);
 int apply_mdagm(qdwf_ctx* ctx, int prec, int layout, void* out, const void* in, void* v,
                 void* te1, void* te2, int nrhs, long rs, hipStream_t st,
                 const int* skip = nullptr, int skip_stride = 0);

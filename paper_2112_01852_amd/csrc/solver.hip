@@ -187,10 +187,11 @@ int reduce_blocks(long n) {
 // ---- operator compositions ---------------------------------------------------
 int apply_hop_parity(qdwf_ctx* ctx, int prec, int layout, int dagger, int out_par, void* out,
                      const void* in, const void* z, double scale, int nrhs, long rs,
-                     hipStream_t st, const int* skip, int skip_stride) {
+                     hipStream_t st, const int* skip, int skip_stride, bool chained) {
   HopArgs a = {};
   a.skip = skip;
   a.skip_stride = skip_stride;
+  a.chained = chained ? 1 : 0;
   a.in[out_par] = in;
   a.out[out_par] = out;
   a.z[out_par] = z;
@@ -214,7 +215,7 @@ int apply_hop_parity(qdwf_ctx* ctx, int prec, int layout, int dagger, int out_pa
 // M_pc^dag applies A^dag once per site inside its hops anyway.
 int apply_mpc(qdwf_ctx* ctx, int prec, int layout, int dagger, void* out, const void* in,
               void* te1, void* te2, int nrhs, long rs, hipStream_t st, const int* skip,
-              int skip_stride, const CgFuse* cg) {
+              int skip_stride, const CgFuse* cg, bool chained) {
   int rc;
   const int chi = dagger ? 0 : 1;
   if (ctx->g.Ls == 16) {
@@ -231,13 +232,14 @@ int apply_mpc(qdwf_ctx* ctx, int prec, int layout, int dagger, void* out, const 
     a.hop_scale = -0.5;
     a.minv = 1;
     a.chi = chi;
+    a.chained = 1;
     a.skip = skip;
     a.skip_stride = skip_stride;
     if ((rc = launch_hop(ctx, prec, layout, dagger, a, st))) return rc;
   } else {
     // te1 = M_eo in  (or (M_oe)^dag in), then te2 = (A/b) M_ee^-1 te1 (or M_ee^-dag te1)
     if ((rc = apply_hop_parity(ctx, prec, layout, dagger, QDWF_EVEN, te1, in, nullptr, -0.5, nrhs,
-                               rs, st, skip, skip_stride)))
+                               rs, st, skip, skip_stride, true)))
       return rc;
     if ((rc = launch_local(ctx, prec, layout, dagger ? MAT_MEEINV_DAG : MAT_AMEEINV, te2, te1, 1, 0,
                            rs, nrhs, st)))
@@ -258,6 +260,7 @@ int apply_mpc(qdwf_ctx* ctx, int prec, int layout, int dagger, void* out, const 
   a.alpha = ctx->act.b * (4.0 - ctx->act.M5) + 1.0;
   a.beta = ctx->act.c * (4.0 - ctx->act.M5) - 1.0;
   a.chi = chi;
+  a.chained = (chained || cg) ? 1 : 0;
   a.skip = skip;
   a.skip_stride = skip_stride;
   if (cg) {
@@ -276,7 +279,8 @@ int apply_mdagm(qdwf_ctx* ctx, int prec, int layout, void* out, const void* in, 
                 void* te1, void* te2, int nrhs, long rs, hipStream_t st, const int* skip,
                 int skip_stride) {
   int rc;
-  if ((rc = apply_mpc(ctx, prec, layout, 0, v, in, te1, te2, nrhs, rs, st, skip, skip_stride)))
+  if ((rc = apply_mpc(ctx, prec, layout, 0, v, in, te1, te2, nrhs, rs, st, skip, skip_stride,
+                      nullptr, true)))
     return rc;
   return apply_mpc(ctx, prec, layout, 1, out, v, te1, te2, nrhs, rs, st, skip, skip_stride);
 }
@@ -737,6 +741,7 @@ static int solve_full(qdwf_ctx* ctx, double* x, const double* b, int nrhs,
     a.npar = 1;
     a.nrhs = nrhs;
     a.hop_scale = -0.5;
+    a.chained = 1;
     return launch_hop(ctx, QDWF_F64, prm.layout, dag, a, st);
   };
   // all FP64 half-field temporaries below have stride n; b and x halves stride 2n
