@@ -13,6 +13,7 @@
 // ones); a backward link is read as its neighbour's forward link. With Ls > 1 the slices of a site
 // share its links and the packed [parity][mu][site] links are read.
 #include "common.h"
+#include "hopcore.h"
 #include "siteio.h"
 #include "spin.h"
 
@@ -72,19 +73,44 @@ struct WilK {
   const int* nbr;      // [2][8][Vh]
   long rs_in, rs_out, rs_z, plane;
   int Vh, Ls, nrhs, par0, npar, epi;
+  int nblk;            // blocks of one half field
+  int nt;              // store the output non-temporally (nt_stores)
   double hop_scale, alpha;
 };
 
+// Launch form by storage type. The kernel is bound by what misses L2: the
+// lanes in flight on an XCD at 16 waves per CU hold 12 MB of spinors and
+// links in FP32, three times its L2, so a neighbour was gone again before the
+// next direction asked for it. Fewer waves, each keeping the loads of the
+// next directions in flight itself, move less (D_h at 32^3 x 64, us; the
+// compiler's own occupancy and order, then this form): FP32 382 -> 256 at two
+// waves per SIMD and two directions ahead (three ahead 256, one wave 282),
+// FP64 733 -> 559 at one wave and two ahead (two waves spill: 693) in blocks
+// of one wavefront (604 in blocks of four), FP16 195 -> 156 at two waves and
+// three ahead (two ahead 165).
+template <class S> struct WilsonForm {
+  static constexpr int waves = sizeof(S) == 8 ? 1 : 2;     // per SIMD
+  static constexpr int ahead = sizeof(S) == 2 ? 3 : 2;     // directions in flight
+  static constexpr int threads = sizeof(S) == 8 ? 64 : 256;
+};
+
 template <class S, int LAYOUT, bool DAG, bool WL>
-__global__ void __launch_bounds__(256) wilson_kernel(WilK k) {
+__global__ void __launch_bounds__(WilsonForm<S>::threads)
+__attribute__((amdgpu_waves_per_eu(WilsonForm<S>::waves, WilsonForm<S>::waves)))
+wilson_kernel(WilK k) {
   typedef typename Store<S>::compute T;
+  constexpr int PD = WilsonForm<S>::ahead;
   const long n5 = (long)k.Vh * k.Ls;
-  const long tid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (tid >= n5 * k.npar * k.nrhs) return;   // no barrier below
-  const long j = tid % n5;
-  const long rp = tid / n5;
-  const int p = k.par0 + (int)(rp % k.npar);
-  const int r = (int)(rp / k.npar);
+  // logical block: parity fastest, then sites, then right-hand sides, each
+  // XCD a contiguous range. Both parities of a region then run together and
+  // read its links once from memory (before: 382 us, with this order alone
+  // 323, FP32 at 32^3 x 64).
+  const int B = xcd_remap(blockIdx.x, gridDim.x);
+  const int p = k.par0 + B % k.npar;
+  const int sb = B / k.npar;
+  const int r = sb / k.nblk;
+  const long j = (long)(sb - r * k.nblk) * blockDim.x + threadIdx.x;
+  if (j >= n5) return;   // no barrier below
   const int q = 1 - p;
   const int i = (int)(j / k.Ls), s = (int)(j - (long)i * k.Ls);
   const int Vh = k.Vh;
@@ -92,28 +118,46 @@ __global__ void __launch_bounds__(256) wilson_kernel(WilK k) {
   const S* lk = reinterpret_cast<const S*>(k.links);
   const int* nb = k.nbr + (long)p * 8 * Vh;
 
+  int nn[8];
+#pragma unroll
+  for (int d = 0; d < 8; ++d) nn[d] = nb[(long)d * Vh + i];
+  // spinor and link of directions D .. D + PD - 1, in buffers D % PD
+  T vb[PD][24], ub[PD][18];
+  auto fetch = [&](auto Dc) __attribute__((always_inline)) {
+    constexpr int D = decltype(Dc)::value;
+    if constexpr (D < 8) {
+      constexpr int MU = D & 3;
+      constexpr bool FWD = D < 4;
+      const int n = nn[D];
+      SiteIO<S, LAYOUT>::load(in, n, s, k.Ls, k.plane, vb[D % PD]);
+      // forward: U_mu(x) of this site; backward: U_mu(x - mu) of the neighbour
+      if constexpr (WL) {
+        WLinkIO<S>::load(reinterpret_cast<const S*>(k.wl), FWD ? p : q, MU, FWD ? i : n, Vh,
+                         ub[D % PD]);
+      } else {
+        const long li = FWD ? (((long)p * 4 + MU) * Vh + i) : (((long)q * 4 + MU) * Vh + n);
+        LinkIO<S>::load(lk + li * 18, ub[D % PD]);
+      }
+    }
+  };
   T acc[24];
-  auto step = [&](auto Dc) {
+  auto step = [&](auto Dc) __attribute__((always_inline)) {
     constexpr int D = decltype(Dc)::value;
     constexpr int MU = D & 3;
     constexpr bool FWD = D < 4;
     // (1 - g) on forward hops and (1 + g) on backward ones; swapped for D_h^dag
     constexpr int SG = (FWD != DAG) ? -1 : +1;
-    const int n = nb[(long)D * Vh + i];
-    T v[24], U[18], h[12], uh[12];
-    SiteIO<S, LAYOUT>::load(in, n, s, k.Ls, k.plane, v);
-    if constexpr (WL) {
-      // forward: U_mu(x) of this site; backward: U_mu(x - mu) of the neighbour
-      WLinkIO<S>::load(reinterpret_cast<const S*>(k.wl), FWD ? p : q, MU, FWD ? i : n, Vh, U);
-    } else {
-      // forward: U_mu(x) of this site; backward: U_mu(x - mu) of the neighbour
-      const long li = FWD ? (((long)p * 4 + MU) * Vh + i) : (((long)q * 4 + MU) * Vh + n);
-      LinkIO<S>::load(lk + li * 18, U);
-    }
-    project<MU, SG>(v, h);
+    T U[18], h[12], uh[12];
+    project<MU, SG>(vb[D % PD], h);
+#pragma unroll
+    for (int c = 0; c < 18; ++c) U[c] = ub[D % PD][c];
+    fetch(IC<D + PD>());
     su3_mul<!FWD>(U, h, uh);
     recon_acc<MU, SG, D == 0>(uh, acc);
   };
+  fetch(IC<0>());
+  fetch(IC<1>());
+  if constexpr (PD > 2) fetch(IC<2>());
   step(IC<0>()); step(IC<1>()); step(IC<2>()); step(IC<3>());
   step(IC<4>()); step(IC<5>()); step(IC<6>()); step(IC<7>());
 
@@ -130,7 +174,8 @@ __global__ void __launch_bounds__(256) wilson_kernel(WilK k) {
     for (int c = 0; c < 24; ++c) acc[c] *= hs;
   }
   S* out = reinterpret_cast<S*>(k.out[p]) + (long)r * k.rs_out;
-  SiteIO<S, LAYOUT>::store(out, i, s, k.Ls, k.plane, acc);
+  if (k.nt) SiteIO<S, LAYOUT>::template store<true>(out, i, s, k.Ls, k.plane, acc);
+  else SiteIO<S, LAYOUT>::store(out, i, s, k.Ls, k.plane, acc);
 }
 
 template <class S, int LAYOUT, bool DAG>
@@ -147,13 +192,16 @@ int run_wilson(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st) {
   k.epi = a.epi;
   k.hop_scale = a.hop_scale;
   k.alpha = a.alpha;
-  const long total = g.n5h * a.npar * a.nrhs;
-  const long blocks = (total + 255) / 256;
+  constexpr int NT = WilsonForm<S>::threads;
+  const long nblk = (g.n5h + NT - 1) / NT;
+  const long blocks = nblk * a.npar * a.nrhs;
+  k.nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0);
+  k.nblk = (int)nblk;
   if (blocks > 0x7fffffffL) return fail(QDWF_EINVAL, "problem too large for one launch");
   if (k.wl)
-    hipLaunchKernelGGL((wilson_kernel<S, LAYOUT, DAG, true>), dim3((unsigned)blocks), dim3(256), 0, st, k);
+    hipLaunchKernelGGL((wilson_kernel<S, LAYOUT, DAG, true>), dim3((unsigned)blocks), dim3(NT), 0, st, k);
   else
-    hipLaunchKernelGGL((wilson_kernel<S, LAYOUT, DAG, false>), dim3((unsigned)blocks), dim3(256), 0, st, k);
+    hipLaunchKernelGGL((wilson_kernel<S, LAYOUT, DAG, false>), dim3((unsigned)blocks), dim3(NT), 0, st, k);
   QDWF_HIP(hipGetLastError());
   return QDWF_OK;
 }
