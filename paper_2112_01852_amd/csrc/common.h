@@ -237,7 +237,7 @@ struct HopArgs {
   int par0, npar;
   int nrhs;
   int epi;
-  int minv;   // 1: apply M_ee^-1 (M_ee^-dag when dagger) to the result; Ls = 16, epi = 0
+  int minv;   // 1: apply M_ee^-1 (M_ee^-dag when dagger) to the result; epi = 0, minv_fused(Ls)
   int chi;    // D_h only (dagger = 0): without minv, in holds (A/b) in, which the hop
               // takes as it is; with minv, the result is multiplied by A/b
   double hop_scale, alpha, beta;

@@ -62,15 +62,15 @@ int run_hop(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st, const Hop
       if (ctx->g.Ls == 16)
         return a.minv ? run_hop_k<S, LAYOUT, false, true, true, true>(ctx, prec, a, st, sh)
                       : run_hop_k<S, LAYOUT, false, true, false, true>(ctx, prec, a, st, sh);
-      if (a.minv) return fail(QDWF_EINVAL, "fused M_ee^-1 needs Ls = 16");
-      return run_hop_k<S, LAYOUT, false, false, false, true>(ctx, prec, a, st, sh);
+      return a.minv ? run_hop_k<S, LAYOUT, false, false, true, true>(ctx, prec, a, st, sh)
+                    : run_hop_k<S, LAYOUT, false, false, false, true>(ctx, prec, a, st, sh);
     }
   }
   if (ctx->g.Ls == 16)
     return a.minv ? run_hop_k<S, LAYOUT, DAG, true, true, false>(ctx, prec, a, st, sh)
                   : run_hop_k<S, LAYOUT, DAG, true, false, false>(ctx, prec, a, st, sh);
-  if (a.minv) return fail(QDWF_EINVAL, "fused M_ee^-1 needs Ls = 16");
-  return run_hop_k<S, LAYOUT, DAG, false, false, false>(ctx, prec, a, st, sh);
+  return a.minv ? run_hop_k<S, LAYOUT, DAG, false, true, false>(ctx, prec, a, st, sh)
+                : run_hop_k<S, LAYOUT, DAG, false, false, false>(ctx, prec, a, st, sh);
 }
 
 }  // namespace

@@ -42,7 +42,8 @@ struct HopK {
   int nsb, nrb, gpw, nrblk;
   int epi, xcd, minv;
   double c_over_b, mf, hop_scale_b, alpha, beta;
-  double rpow[4];      // (-beta/alpha)^(2^j), j < 4: the M_ee^-1 scan
+  int nd, md;          // M_ee^-1 scan: Ls = 2^nd md, md odd
+  double rpow[6];      // (-beta/alpha)^(2^j), j <= nd
   const int* skip;     // per-rhs skip flags (HopArgs::skip), or nullptr
   int skip_stride;
   int cg;              // fused CG step (HopArgs::cg)
@@ -311,13 +312,14 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
     for (int i = 0; i < 24; ++i) acc[i] = tmp[i];
   }
   if constexpr (MINV) {
-    {
-      // out = M_ee^-1 (or M_ee^-dag) applied to the hop result, across the 16
-      // slices of the row: (alpha + beta S)^-1 on each chirality is a cyclic
-      // geometric series in S, summed by doubling (steps 1, 2, 4, 8), with -mf
-      // on the terms that wrap; its common factor is folded into the scale.
-      // M_ee: upper spins see S_d (slice s - d), lower spins S_u (s + d);
-      // the adjoint swaps them.
+    // out = M_ee^-1 (or M_ee^-dag) applied to the hop result, across the
+    // slices of the group: (alpha + beta S)^-1 on each chirality is a cyclic
+    // geometric series in S, (1 / alpha) sum over k < Ls of rho^k S^k with
+    // -mf on the terms that wrap; its common factor is folded into the scale.
+    // M_ee: upper spins see S_d (slice s - d), lower spins S_u (s + d); the
+    // adjoint swaps them.
+    if constexpr (DPP16) {
+      // summed by doubling (steps 1, 2, 4, 8)
       auto scan = [&](auto Jc) {
         constexpr int J = decltype(Jc)::value;
         constexpr int Dd = 1 << J;
@@ -331,6 +333,60 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
         else shift_s<Dd, 16 - Dd>(sh, cdn, cup, src, acc);
       };
       scan(IC<0>()); scan(IC<1>()); scan(IC<2>()); scan(IC<3>());
+    } else {
+      // Ls = 2^nd md: nd doublings, then the md terms of step 2^nd at once
+      auto shifted = [&](int d, T rp, T& cdn, T& cup, int& ldn, int& lup) __attribute__((always_inline)) {
+        const int dn = s - d, up = s + d;
+        cdn = dn < 0 ? rp * (-mf) : rp;
+        cup = up >= Ls ? rp * (-mf) : rp;
+        ldn = lane_ok ? base + (dn < 0 ? dn + Ls : dn) : lane;
+        lup = lane_ok ? base + (up >= Ls ? up - Ls : up) : lane;
+        if constexpr (DAG) {
+          const T c = cdn; cdn = cup; cup = c;
+          const int l = ldn; ldn = lup; lup = l;
+        }
+      };
+      for (int j = 0; j < k.nd; ++j) {
+        T cl, ch;
+        int ll, lh;
+        shifted(1 << j, (T)k.rpow[j], cl, ch, ll, lh);
+#pragma unroll
+        for (int i = 0; i < 24; ++i)
+          acc[i] = fmac(i < 12 ? cl : ch, (T)__shfl(acc[i], i < 12 ? ll : lh, 64), acc[i]);
+      }
+      if (k.md == 3) {
+        // Ls = 12, 24 (and 6, 3): both terms of a component together
+        T cl, ch, cl2, ch2;
+        int ll, lh, ll2, lh2;
+        const T rp = (T)k.rpow[k.nd];
+        shifted(1 << k.nd, rp, cl, ch, ll, lh);
+        shifted(2 << k.nd, rp * rp, cl2, ch2, ll2, lh2);
+#pragma unroll
+        for (int i = 0; i < 24; ++i) {
+          const T v = acc[i];
+          acc[i] = fmac(i < 12 ? cl2 : ch2, (T)__shfl(v, i < 12 ? ll2 : lh2, 64),
+                        fmac(i < 12 ? cl : ch, (T)__shfl(v, i < 12 ? ll : lh, 64), v));
+        }
+      } else if (k.md > 1) {
+        // Ls = 10, 20 (md = 5) and 5
+        T cl[4], ch[4];
+        int ll[4], lh[4];
+        T rp = (T)1;
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+          rp *= (T)k.rpow[k.nd];
+          shifted((m + 1) << k.nd, rp, cl[m], ch[m], ll[m], lh[m]);
+        }
+#pragma unroll
+        for (int i = 0; i < 24; ++i) {
+          const T v = acc[i];
+          T t = v;
+#pragma unroll
+          for (int m = 0; m < 4; ++m)
+            t = fmac(i < 12 ? cl[m] : ch[m], (T)__shfl(v, i < 12 ? ll[m] : lh[m], 64), t);
+          acc[i] = t;
+        }
+      }
     }
     if constexpr (CHI) {
       // chi / b of the result for the next hop: (1 + (c/b) C) M_ee^-1 h
@@ -453,9 +509,28 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
 }
 
 
+// Ls = 2^nd md with md odd: the steps of the fused M_ee^-1.
+inline void minv_steps(int Ls, int* nd, int* md) {
+  *nd = 0;
+  while (Ls % 2 == 0) {
+    Ls /= 2;
+    ++*nd;
+  }
+  *md = Ls;
+}
+// Whether the hop takes M_ee^-1 with it at this Ls: the series then costs at
+// most six shifts of the result (Ls = 8: 3, 12: 4, 16: 4, 20: 6, 24: 5), less
+// than writing the hop's result and reading it in a launch of its own. Other
+// Ls (odd factor 7 or more) keep launch_local.
+inline bool minv_fused(int Ls) {
+  int nd, md;
+  minv_steps(Ls, &nd, &md);
+  return md <= 5 && nd <= 5;
+}
+
 // Kernel arguments of a hop launch on one context (HopArgs as for
 // launch_hop, the launch shape sh), its LDS bytes per block and its number of
-// logical blocks. MINV: M_ee^-1 fused (Ls = 16 only).
+// logical blocks. MINV: M_ee^-1 fused (minv_fused).
 template <class S, bool MINV>
 int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& sh, HopK* k,
               size_t* lds, int* nblocks) {
@@ -494,14 +569,20 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
   k->minv = MINV;
   if (MINV) {
     if (a.epi) return fail(QDWF_EINVAL, "fused M_ee^-1 takes no epilogue term");
+    if (!minv_fused(g.Ls)) return fail(QDWF_EINVAL, "fused M_ee^-1 does not take Ls = %d", g.Ls);
     const double al = ctx->act.b * (4.0 - ctx->act.M5) + 1.0;
     const double be = ctx->act.c * (4.0 - ctx->act.M5) - 1.0;
+    minv_steps(g.Ls, &k->nd, &k->md);
     double r = -be / al;
-    for (int j = 0; j < 4; ++j) { k->rpow[j] = r; r *= r; }
-    // r is now (-beta/alpha)^16 = (-beta/alpha)^Ls
-    k->hop_scale_b /= al * (1.0 + ctx->act.mf * r);
+    for (int j = 0; j < 6; ++j) { k->rpow[j] = r; r *= r; }
+    // (-beta/alpha)^Ls from its 2^nd-th power
+    double rl = 1.0;
+    for (int m = 0; m < k->md; ++m) rl *= k->rpow[k->nd];
+    k->hop_scale_b /= al * (1.0 + ctx->act.mf * rl);
   } else {
-    for (int j = 0; j < 4; ++j) k->rpow[j] = 0.0;
+    k->nd = 0;
+    k->md = 1;
+    for (int j = 0; j < 6; ++j) k->rpow[j] = 0.0;
   }
   // links, neighbour table, then (fused CG step) one double per thread
   *lds = (size_t)8 * LinkStride<T>::v * k->nsb * sizeof(T) + (size_t)8 * k->nsb * sizeof(int) +

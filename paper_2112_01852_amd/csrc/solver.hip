@@ -27,6 +27,7 @@
 #include <cstddef>
 
 #include "cgbody.h"
+#include "hopbody.h"
 
 namespace qdwf {
 
@@ -218,10 +219,9 @@ int apply_mpc(qdwf_ctx* ctx, int prec, int layout, int dagger, void* out, const 
               int skip_stride, const CgFuse* cg, bool chained) {
   int rc;
   const int chi = dagger ? 0 : 1;
-  if (ctx->g.Ls == 16) {
+  if (minv_fused(ctx->g.Ls)) {
     // te2 = M_ee^-1 M_eo in (times A/b), or M_ee^-dag (M_oe)^dag in, in one
-    // launch: the hop's 16 slices of a site share a DPP row, where M_ee^-1 is
-    // a scan
+    // launch: the slices of a site share a wavefront, where M_ee^-1 is a scan
     HopArgs a = {};
     a.in[QDWF_EVEN] = in;
     a.out[QDWF_EVEN] = te2;
