@@ -64,11 +64,17 @@ class GroupEngine {
 
  private:
   GroupEngine() = default;
-  int capture(hipStream_t cs);
+  int capture(hipStream_t cs, int c);
   int device_ = 0, inner_ = 0, layout_ = 0, k_ = 1;
   void* table_ = nullptr;     // device
   void* staging_ = nullptr;   // pinned host copy of the table
-  hipGraphExec_t exec_ = nullptr;
+  // per class of members (group.hip): its captured round, how many members
+  // it has, and the stream and event its round runs on beside the first's
+  static constexpr int kClasses = 3;
+  hipGraphExec_t exec_[kClasses] = {};
+  int present_[kClasses] = {};
+  hipStream_t aux_[kClasses] = {};
+  hipEvent_t join_[kClasses] = {}, fork_ = nullptr;
 };
 
 size_t group_table_bytes();

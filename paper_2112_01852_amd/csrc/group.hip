@@ -21,10 +21,27 @@ constexpr int kLocalGrid = 1024;
 constexpr int kBlasGrid = 2048;    // blocks of a grouped vector launch (RT threads)
 constexpr int kLsMin = 8, kLsMax = 32;   // Ls a group accepts
 
-// Units of one kind of grouped launch: member j owns [start[j], start[j+1]).
+// Members come in classes, each advanced by its own chain of launches: the
+// members of one class run the same hop kernel.
+enum {
+  CLS_16 = 0,      // Ls = 16: slices in DPP rows
+  CLS_FUSED = 1,   // other Ls whose M_ee^-1 the hop takes with it (minv_fused)
+  CLS_LOCAL = 2,   // the rest: M_ee^-1 in g_local launches
+  CLS_COUNT = 3
+};
+static_assert(CLS_COUNT == 3, "GroupEngine::kClasses");
+inline int class_of(int Ls) { return Ls == 16 ? CLS_16 : minv_fused(Ls) ? CLS_FUSED : CLS_LOCAL; }
+
+// Units of one kind of grouped launch over a class: its member i owns
+// [start[i], start[i+1]).
 struct UnitHdr {
-  int n;
   int start[kGroupMax + 1];
+};
+
+// A class: members [first, first + n) of the table and their units.
+struct ClassHdr {
+  int first, n;
+  UnitHdr blas, hop, loc, sites;
 };
 
 // A member's vectors and scalars as the grouped vector kernels see them.
@@ -51,7 +68,7 @@ struct GReq {
   double tol2, delta2;
 };
 
-// M_ee^-1 (or M_ee^-dag) of a member with Ls != 16, between the hop stages.
+// M_ee^-1 (or M_ee^-dag) of a member of CLS_LOCAL, between the hop stages.
 struct GLoc {
   const void* in;
   void* out;
@@ -61,7 +78,7 @@ struct GLoc {
 };
 
 struct Table {
-  UnitHdr blas, one, hop16, hopg, loc, sites;   // hop16: Ls = 16 members, hopg: the others
+  ClassHdr cls[CLS_COUNT];
   GReq req[kGroupMax];
   HopK hop_s[4][kGroupMax];   // M_pc^dag M_pc stages in the inner precision
   HopK hop_d[4][kGroupMax];   // the same in FP64 (reliable updates)
@@ -69,24 +86,34 @@ struct Table {
   GLoc loc_d[2][kGroupMax];
 };
 
-__device__ inline int member_of(const UnitHdr& h, int u) {
-  // largest j with start[j] <= u (members without units are skipped over)
-  int lo = 0, hi = h.n;
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (h.start[mid] <= u) lo = mid;
-    else hi = mid;
+// The units of a class as a wavefront walks them: lane i holds the first unit
+// of the class's member i and its status when the kernel began, so a unit's
+// member is found and tested without touching memory, and a launch with
+// nothing to do (a reliable update nobody asked for) ends after two loads.
+struct Units {
+  int first, start, status, total;
+  __device__ inline Units(const Table* __restrict__ t, const ClassHdr& c, const UnitHdr& h) {
+    const int lane = threadIdx.x & 63;
+    const bool mine = lane < c.n;
+    first = c.first;
+    start = mine ? h.start[lane] : 0x7fffffff;
+    status = mine ? t->req[c.first + lane].st->status : -1;
+    total = h.start[c.n];
   }
-  return lo;
-}
+  __device__ inline bool any(int want) const { return __any(status == want); }
+  // member (index in its class) that owns unit u: the last one that starts at
+  // or before it (members without units share their successor's start)
+  __device__ inline int owner(int u) const { return __popcll(__ballot(start <= u)) - 1; }
+  __device__ inline int status_of(int i) const { return __builtin_amdgcn_readlane(status, i); }
+  __device__ inline int start_of(int i) const { return __builtin_amdgcn_readlane(start, i); }
+};
 
 // ---- grouped kernels ---------------------------------------------------------
-// Hop stage `stage` (0..3) of M_pc^dag M_pc for the members whose status is
-// `want`; FP64: the reliable update's operator. DPP16: the members with
-// Ls = 16 (slices in DPP rows; MINV fuses M_ee^-1 into stages 0 and 2), else
-// the other members (cross-lane permutes; stages 0 and 2 write te1 for
-// g_local). One kernel per form: a kernel holding both bodies runs out of
-// registers.
+// Hop stage `stage` (0..3) of M_pc^dag M_pc for the members of class c whose
+// status is `want`; FP64: the reliable update's operator. DPP16: Ls = 16
+// (slices in DPP rows), else cross-lane permutes; MINV fuses M_ee^-1 into
+// stages 0 and 2 (without it they write te1 for g_local). One kernel per
+// form: a kernel holding two bodies runs out of registers.
 // Waves per SIMD the grouped hop's registers are planned for, so that no
 // form spills: FP64 two on DPP rows in the interleaved layout (253-256
 // registers) and one otherwise (its permute form needs more than the 256
@@ -106,69 +133,70 @@ template <class S, int LAYOUT, bool DPP16> struct GroupWaves {
 template <class S, int LAYOUT, bool DAG, bool DPP16, bool MINV, bool CHI>
 __global__ void __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(GroupWaves<S, LAYOUT, DPP16>::v, GroupWaves<S, LAYOUT, DPP16>::v)))
-g_hop(const Table* __restrict__ t, int stage, int fp64, int want) {
+g_hop(const Table* __restrict__ t, int c, int stage, int fp64, int want) {
   extern __shared__ __align__(16) unsigned char smem[];
-  const UnitHdr& h = DPP16 ? t->hop16 : t->hopg;
-  const int total = h.start[h.n];
-  const HopK* tab = fp64 ? t->hop_d[stage] : t->hop_s[stage];
-  for (int u = blockIdx.x; u < total; u += gridDim.x) {
-    const int j = member_of(h, u);
-    if (t->req[j].st->status != want) continue;
-    hop_block<S, LAYOUT, DAG, DPP16, MINV, CHI>(tab[j], u - h.start[j], smem);
+  const Units un(t, t->cls[c], t->cls[c].hop);
+  if (!un.any(want)) return;
+  const HopK* tab = (fp64 ? t->hop_d[stage] : t->hop_s[stage]) + un.first;
+  for (int u = blockIdx.x; u < un.total; u += gridDim.x) {
+    const int j = un.owner(u);
+    if (un.status_of(j) != want) continue;
+    hop_block<S, LAYOUT, DAG, DPP16, MINV, CHI>(tab[j], u - un.start_of(j), smem);
     __syncthreads();
   }
 }
 
 template <class S, int LAYOUT>
 __global__ void __launch_bounds__(kLocalThreads)
-g_local(const Table* __restrict__ t, int which, int fp64, int want) {
+g_local(const Table* __restrict__ t, int c, int which, int fp64, int want) {
   typedef typename Store<S>::compute T;
   extern __shared__ __align__(16) unsigned char smem[];
-  const UnitHdr& h = t->loc;
-  const int total = h.start[h.n];
-  const GLoc* tab = fp64 ? t->loc_d[which] : t->loc_s[which];
-  for (int u = blockIdx.x; u < total; u += gridDim.x) {
-    const int j = member_of(h, u);
-    if (t->req[j].st->status != want) continue;
+  const Units un(t, t->cls[c], t->cls[c].loc);
+  if (!un.any(want)) return;
+  const GLoc* tab = (fp64 ? t->loc_d[which] : t->loc_s[which]) + un.first;
+  for (int u = blockIdx.x; u < un.total; u += gridDim.x) {
+    const int j = un.owner(u);
+    if (un.status_of(j) != want) continue;
     const GLoc& l = tab[j];
     local_block<S, LAYOUT>(reinterpret_cast<const S*>(l.in), reinterpret_cast<S*>(l.out),
-                           reinterpret_cast<const T*>(l.K), l.Vh, l.Ls, l.plane, u - h.start[j],
+                           reinterpret_cast<const T*>(l.K), l.Vh, l.Ls, l.plane, u - un.start_of(j),
                            smem);
     __syncthreads();
   }
 }
 
-#define GROUP_LOOP(HDR)                                       \
-  const UnitHdr& h = t->HDR;                                  \
-  const int total = h.start[h.n];                             \
-  for (int u = blockIdx.x; u < total; u += gridDim.x) {       \
-    const int j = member_of(h, u);                            \
-    const GReq& r = t->req[j];                                \
-    const int bx = u - h.start[j];
+// Walks the units (kind HDR) of the members of class c whose status is WANT.
+#define GROUP_LOOP(HDR, WANT)                                 \
+  const Units un(t, t->cls[c], t->cls[c].HDR);                \
+  if (!un.any(WANT)) return;                                  \
+  for (int u = blockIdx.x; u < un.total; u += gridDim.x) {    \
+    const int j = un.owner(u);                                \
+    if (un.status_of(j) != (WANT)) continue;                  \
+    const GReq& r = t->req[un.first + j];                     \
+    const int bx = u - un.start_of(j);
 
 // The fused iteration's reductions of the per-site sums (|M_pc p|^2, then
 // |r|^2), alpha and beta as in the single-context solver, and the p pass
 // (x takes its step in the last hop of M_pc^dag).
-__global__ void __launch_bounds__(RT) g_sum_sites(const Table* __restrict__ t) {
+__global__ void __launch_bounds__(RT) g_sum_sites(const Table* __restrict__ t, int c) {
   __shared__ double sh[RT];
-  GROUP_LOOP(sites)
-    if (r.st->status != ST_RUN) continue;
+  GROUP_LOOP(sites, ST_RUN)
     k_sum_body(r.site, r.nsite, r.part, bx, r.NBs, 0, sh);
   }
 }
 
-__global__ void __launch_bounds__(RT) g_alpha(const Table* __restrict__ t) {
+__global__ void __launch_bounds__(RT) g_alpha(const Table* __restrict__ t, int c) {
   __shared__ double sh[RT];
-  for (int j = blockIdx.x; j < t->one.n; j += gridDim.x) {
-    const GReq& r = t->req[j];
+  for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
+    const GReq& r = t->req[t->cls[c].first + j];
     k_alpha_body(r.part, r.NBs, r.st, 0, sh);
   }
 }
 
-__global__ void __launch_bounds__(RT) g_beta(const Table* __restrict__ t) {
+__global__ void __launch_bounds__(RT) g_beta(const Table* __restrict__ t, int c) {
   __shared__ double sh[RT];
-  for (int j = blockIdx.x; j < t->one.n; j += gridDim.x) {
-    const GReq& r = t->req[j];
+  for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
+    const GReq& r = t->req[t->cls[c].first + j];
     k_beta_body(r.part, r.NBs, r.st, r.delta2, 0, sh);
   }
 }
@@ -176,43 +204,44 @@ __global__ void __launch_bounds__(RT) g_beta(const Table* __restrict__ t) {
 // p = r + beta p in place while the member keeps running (its x took the
 // iteration's step in the last hop of M_pc^dag)
 template <class S>
-__global__ void __launch_bounds__(RT) g_update_p(const Table* __restrict__ t) {
+__global__ void __launch_bounds__(RT) g_update_p(const Table* __restrict__ t, int c) {
   typedef typename ResidStore<S>::t RR;
-  GROUP_LOOP(blas)
+  GROUP_LOOP(blas, ST_RUN)
     k_grp_p_body<RR, S>(reinterpret_cast<const RR*>(r.rl), reinterpret_cast<S*>(r.p), 0, 0, r.n,
                         r.n, r.st, r.vec_s && r.vec_r, bx, r.NB, 0);
   }
 }
 
 template <class R>
-__global__ void __launch_bounds__(RT) g_fold_x(const Table* __restrict__ t) {
-  GROUP_LOOP(blas)
+__global__ void __launch_bounds__(RT) g_fold_x(const Table* __restrict__ t, int c) {
+  GROUP_LOOP(blas, ST_UPDATE)
     k_fold_x_body<R>(r.xh, reinterpret_cast<R*>(r.xl), r.n, r.n, r.n, r.st, bx, r.NB, 0, nullptr);
   }
 }
 
-__global__ void __launch_bounds__(RT) g_resid(const Table* __restrict__ t) {
+__global__ void __launch_bounds__(RT) g_resid(const Table* __restrict__ t, int c) {
   __shared__ double sh[RT];
-  GROUP_LOOP(blas)
-    if (r.st->status != ST_UPDATE) continue;
+  GROUP_LOOP(blas, ST_UPDATE)
     k_resid_body(r.b, r.ax, r.rh, r.n, r.n, r.n, r.part, bx, r.NB, 0, sh);
   }
 }
 
-__global__ void __launch_bounds__(RT) g_ru_decide(const Table* __restrict__ t) {
+__global__ void __launch_bounds__(RT) g_ru_decide(const Table* __restrict__ t, int c) {
   __shared__ double sh[RT];
-  for (int j = blockIdx.x; j < t->one.n; j += gridDim.x) {
-    const GReq& r = t->req[j];
+  for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
+    const GReq& r = t->req[t->cls[c].first + j];
     const int first = r.st->first;
     __syncthreads();   // every thread has read `first` before the body may clear it
     k_ru_decide_body(r.part, r.NB, r.st, r.tol2, (double)r.n, r.scale, first, 0, sh);
   }
 }
 
+// (a member that runs without a fresh reliable update is skipped by the body)
 template <class S, class R>
-__global__ void __launch_bounds__(RT) g_ru_apply(const Table* __restrict__ t) {
+__global__ void __launch_bounds__(RT) g_ru_apply(const Table* __restrict__ t, int c) {
   typedef typename ResidStore<S>::t RR;
-  GROUP_LOOP(blas)
+  GROUP_LOOP(blas, ST_RUN)
+    if (!r.st->fresh) continue;
     k_ru_apply_body<RR, S>(r.rh, reinterpret_cast<RR*>(r.rl), reinterpret_cast<S*>(r.p), r.n, r.n,
                           r.st, bx, r.NB, 0, nullptr);
   }
@@ -263,9 +292,18 @@ size_t local_lds_max(size_t real_bytes) {
   return m;
 }
 
-// The launches of one round: k x [reliable update; iteration].
+// A reliable update is offered every kUpdateEvery iterations of a round. A
+// member that asks for one waits for the next offer (at most three
+// iterations, on average one and a half of some 25 between its updates in
+// FP16); its own sequence of iterations and updates, and so its result, does
+// not change. Offering it before every iteration instead costs eight
+// launches that nearly always find nothing to do.
+constexpr int kUpdateEvery = 4;
+
+// The launches of one round of class c: k iterations, with reliable updates
+// offered every kUpdateEvery of them.
 template <class S, class R, int LAYOUT>
-int record_round(const Table* t, int k, hipStream_t st) {
+int record_round(const Table* t, int c, int k, hipStream_t st) {
   typedef typename Store<S>::compute T;
   const size_t lds_s = hop_lds_max(sizeof(T), LinkStride<T>::v, true);
   const size_t lds_d = hop_lds_max(sizeof(double), LinkStride<double>::v, false);
@@ -273,42 +311,57 @@ int record_round(const Table* t, int k, hipStream_t st) {
   const size_t loc_d = local_lds_max(sizeof(double));
   const dim3 hg(kHopGrid), hb(256), lg(kLocalGrid), lb(kLocalThreads), bg(kBlasGrid), bb(RT),
       og(kGroupMax);
-  // M_pc (mid: between its two hops, for the fused CG step's reductions)
-  // and M_pc^dag
+  // M_pc (its first stage hands the second chi = (A/b) M_ee^-1 M_eo p) and
+  // M_pc^dag
   auto mpc = [&](auto stag, size_t lds, size_t llds, int fp64, int want) {
     typedef decltype(stag) P;
-    // its first stage hands the second chi = (A/b) M_ee^-1 M_eo p
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, false, true, true, true>), hg, hb, lds, st, t, 0, fp64, want);
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, false, false, false, false>), hg, hb, lds, st, t, 0, fp64, want);
-    hipLaunchKernelGGL((g_local<P, LAYOUT>), lg, lb, llds, st, t, 0, fp64, want);
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, false, true, false, true>), hg, hb, lds, st, t, 1, fp64, want);
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, false, false, false, true>), hg, hb, lds, st, t, 1, fp64, want);
+    if (c == CLS_16) {
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, false, true, true, true>), hg, hb, lds, st, t, c, 0, fp64, want);
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, false, true, false, true>), hg, hb, lds, st, t, c, 1, fp64, want);
+      return;
+    }
+    if (c == CLS_FUSED) {
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, false, false, true, true>), hg, hb, lds, st, t, c, 0, fp64, want);
+    } else {
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, false, false, false, false>), hg, hb, lds, st, t, c, 0, fp64, want);
+      hipLaunchKernelGGL((g_local<P, LAYOUT>), lg, lb, llds, st, t, c, 0, fp64, want);
+    }
+    hipLaunchKernelGGL((g_hop<P, LAYOUT, false, false, false, true>), hg, hb, lds, st, t, c, 1, fp64, want);
   };
   auto mpc_dag = [&](auto stag, size_t lds, size_t llds, int fp64, int want) {
     typedef decltype(stag) P;
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, true, true, true, false>), hg, hb, lds, st, t, 2, fp64, want);
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, true, false, false, false>), hg, hb, lds, st, t, 2, fp64, want);
-    hipLaunchKernelGGL((g_local<P, LAYOUT>), lg, lb, llds, st, t, 1, fp64, want);
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, true, true, false, false>), hg, hb, lds, st, t, 3, fp64, want);
-    hipLaunchKernelGGL((g_hop<P, LAYOUT, true, false, false, false>), hg, hb, lds, st, t, 3, fp64, want);
+    if (c == CLS_16) {
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, true, true, true, false>), hg, hb, lds, st, t, c, 2, fp64, want);
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, true, true, false, false>), hg, hb, lds, st, t, c, 3, fp64, want);
+      return;
+    }
+    if (c == CLS_FUSED) {
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, true, false, true, false>), hg, hb, lds, st, t, c, 2, fp64, want);
+    } else {
+      hipLaunchKernelGGL((g_hop<P, LAYOUT, true, false, false, false>), hg, hb, lds, st, t, c, 2, fp64, want);
+      hipLaunchKernelGGL((g_local<P, LAYOUT>), lg, lb, llds, st, t, c, 1, fp64, want);
+    }
+    hipLaunchKernelGGL((g_hop<P, LAYOUT, true, false, false, false>), hg, hb, lds, st, t, c, 3, fp64, want);
   };
   for (int i = 0; i < k; ++i) {
-    // reliable update of the members that asked for one (and the initial one)
-    hipLaunchKernelGGL((g_fold_x<R>), bg, bb, 0, st, t);
-    mpc(double(), lds_d, loc_d, 1, ST_UPDATE);
-    mpc_dag(double(), lds_d, loc_d, 1, ST_UPDATE);
-    hipLaunchKernelGGL(g_resid, bg, bb, 0, st, t);
-    hipLaunchKernelGGL(g_ru_decide, og, bb, 0, st, t);
-    hipLaunchKernelGGL((g_ru_apply<S, R>), bg, bb, 0, st, t);
+    if (i % kUpdateEvery == 0) {
+      // reliable update of the members that asked for one (and the initial one)
+      hipLaunchKernelGGL((g_fold_x<R>), bg, bb, 0, st, t, c);
+      mpc(double(), lds_d, loc_d, 1, ST_UPDATE);
+      mpc_dag(double(), lds_d, loc_d, 1, ST_UPDATE);
+      hipLaunchKernelGGL(g_resid, bg, bb, 0, st, t, c);
+      hipLaunchKernelGGL(g_ru_decide, og, bb, 0, st, t, c);
+      hipLaunchKernelGGL((g_ru_apply<S, R>), bg, bb, 0, st, t, c);
+    }
     // one iteration of the running members, its vector steps fused into
     // the last hops of M_pc and M_pc^dag
     mpc(S(), lds_s, loc_s, 0, ST_RUN);
-    hipLaunchKernelGGL(g_sum_sites, bg, bb, 0, st, t);
-    hipLaunchKernelGGL(g_alpha, og, bb, 0, st, t);
+    hipLaunchKernelGGL(g_sum_sites, bg, bb, 0, st, t, c);
+    hipLaunchKernelGGL(g_alpha, og, bb, 0, st, t, c);
     mpc_dag(S(), lds_s, loc_s, 0, ST_RUN);
-    hipLaunchKernelGGL(g_sum_sites, bg, bb, 0, st, t);
-    hipLaunchKernelGGL(g_beta, og, bb, 0, st, t);
-    hipLaunchKernelGGL((g_update_p<S>), bg, bb, 0, st, t);
+    hipLaunchKernelGGL(g_sum_sites, bg, bb, 0, st, t, c);
+    hipLaunchKernelGGL(g_beta, og, bb, 0, st, t, c);
+    hipLaunchKernelGGL((g_update_p<S>), bg, bb, 0, st, t, c);
   }
   QDWF_HIP(hipGetLastError());
   return QDWF_OK;
@@ -355,7 +408,7 @@ int fill_mdagm(qdwf_ctx* ctx, int prec, const void* in, void* out, void* v, void
                HopK* hk[4], GLoc* lk[2], const CgFuse* cg = nullptr) {
   const Geom& g = ctx->g;
   const long rs = g.n5h * 24;
-  const bool ls16 = g.Ls == 16;
+  const bool fused = minv_fused(g.Ls);
   const double al = ctx->act.b * (4.0 - ctx->act.M5) + 1.0;
   const double be = ctx->act.c * (4.0 - ctx->act.M5) - 1.0;
   int rc;
@@ -364,14 +417,14 @@ int fill_mdagm(qdwf_ctx* ctx, int prec, const void* in, void* out, void* v, void
     void* dst = dag ? out : v;
     HopArgs a = {};
     a.in[QDWF_EVEN] = src;
-    a.out[QDWF_EVEN] = ls16 ? te2 : te1;
+    a.out[QDWF_EVEN] = fused ? te2 : te1;
     a.rs_in = a.rs_out = a.rs_z = rs;
     a.par0 = QDWF_EVEN;
     a.npar = 1;
     a.nrhs = 1;
     a.hop_scale = -0.5;
-    a.minv = ls16 ? 1 : 0;
-    a.chi = (ls16 && !dag) ? 1 : 0;
+    a.minv = fused ? 1 : 0;
+    a.chi = (fused && !dag) ? 1 : 0;
     a.chained = 1;
     if ((rc = fill_hop(ctx, prec, a, hk[2 * dag]))) return rc;
     GLoc& l = *lk[dag];
@@ -433,7 +486,14 @@ int GroupEngine::create(int device, int inner, int layout, int k, void* table_me
     return fail(QDWF_ENOMEM, "pinned host staging of %zu bytes failed", sizeof(Table));
   }
   std::memset(e->staging_, 0, sizeof(Table));
-  int rc = e->capture(capture);
+  int rc = QDWF_OK;
+  for (int c = 0; c < CLS_COUNT && !rc; ++c) rc = e->capture(capture, c);
+  for (int c = 1; c < CLS_COUNT && !rc; ++c)
+    if (hipStreamCreateWithFlags(&e->aux_[c], hipStreamNonBlocking) != hipSuccess ||
+        hipEventCreateWithFlags(&e->join_[c], hipEventDisableTiming) != hipSuccess)
+      rc = fail(QDWF_EDEVICE, "stream or event creation failed");
+  if (!rc && hipEventCreateWithFlags(&e->fork_, hipEventDisableTiming) != hipSuccess)
+    rc = fail(QDWF_EDEVICE, "event creation failed");
   if (rc) {
     delete e;
     return rc;
@@ -442,11 +502,11 @@ int GroupEngine::create(int device, int inner, int layout, int k, void* table_me
   return QDWF_OK;
 }
 
-int GroupEngine::capture(hipStream_t cs) {
+int GroupEngine::capture(hipStream_t cs, int c) {
   QDWF_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
   const Table* t = reinterpret_cast<const Table*>(table_);
   int rc = by_types(inner_, layout_, [&](auto stag, auto rtag, auto lay) -> int {
-    return record_round<decltype(stag), decltype(rtag), decltype(lay)::value>(t, k_, cs);
+    return record_round<decltype(stag), decltype(rtag), decltype(lay)::value>(t, c, k_, cs);
   });
   hipGraph_t graph = nullptr;
   const hipError_t e = hipStreamEndCapture(cs, &graph);
@@ -455,39 +515,53 @@ int GroupEngine::capture(hipStream_t cs) {
     return rc;
   }
   if (e != hipSuccess) return fail(QDWF_EDEVICE, "capture of the round failed: %s", hipGetErrorString(e));
-  const hipError_t e2 = hipGraphInstantiate(&exec_, graph, nullptr, nullptr, 0);
+  const hipError_t e2 = hipGraphInstantiate(&exec_[c], graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
   if (e2 != hipSuccess) {
-    exec_ = nullptr;
+    exec_[c] = nullptr;
     return fail(QDWF_EDEVICE, "instantiation of the round failed: %s", hipGetErrorString(e2));
   }
   return QDWF_OK;
 }
 
 GroupEngine::~GroupEngine() {
-  if (exec_) (void)hipGraphExecDestroy(exec_);
+  for (int c = 0; c < CLS_COUNT; ++c) {
+    if (exec_[c]) (void)hipGraphExecDestroy(exec_[c]);
+    if (aux_[c]) (void)hipStreamDestroy(aux_[c]);
+    if (join_[c]) (void)hipEventDestroy(join_[c]);
+  }
+  if (fork_) (void)hipEventDestroy(fork_);
   if (staging_) (void)hipHostFree(staging_);
 }
 
 int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
   if (n < 0 || n > kGroupMax) return fail(QDWF_EINVAL, "%d members, at most %d", n, kGroupMax);
   Table& T = *reinterpret_cast<Table*>(staging_);
-  T.blas.n = T.one.n = T.hop16.n = T.hopg.n = T.loc.n = T.sites.n = n;
-  T.blas.start[0] = T.one.start[0] = T.hop16.start[0] = T.hopg.start[0] = T.loc.start[0] =
-      T.sites.start[0] = 0;
+  // the table lists the members class by class
+  int order[kGroupMax], listed = 0;
+  for (int c = 0; c < CLS_COUNT; ++c) {
+    ClassHdr& C = T.cls[c];
+    C.first = listed;
+    for (int j = 0; j < n; ++j)
+      if (class_of(m[j].ctx->g.Ls) == c) order[listed++] = j;
+    C.n = listed - C.first;
+    present_[c] = C.n;
+    C.blas.start[0] = C.hop.start[0] = C.loc.start[0] = C.sites.start[0] = 0;
+  }
   const size_t ps = prec_bytes(inner_);
   const size_t rsz = inner_ == QDWF_F64 ? 8 : 4;
   int rc;
   for (int j = 0; j < n; ++j) {
-    qdwf_ctx* c = m[j].ctx;
+    const GroupMember& mj = m[order[j]];
+    qdwf_ctx* c = mj.ctx;
     const Geom& g = c->g;
     if (g.Ls < kLsMin || g.Ls > kLsMax)
       return fail(QDWF_EINVAL, "grouped solves take %d <= Ls <= %d (got %d)", kLsMin, kLsMax, g.Ls);
     const long n5 = g.n5h * 24;
     const Layout L = solver_layout(n5, 1, inner_);
-    char* w = m[j].ws;
+    char* w = mj.ws;
     GReq& r = T.req[j];
-    r.st = m[j].st;
+    r.st = mj.st;
     r.n = n5;
     r.NB = reduce_blocks(n5);
     r.nsite = g.Vh;
@@ -498,8 +572,8 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     r.rl = w + L.off_rl;
     r.p = w + L.off_p;
     r.ap = w + L.off_ap;
-    r.xh = m[j].xo;
-    r.b = m[j].bo;
+    r.xh = mj.xo;
+    r.b = mj.bo;
     r.rh = reinterpret_cast<double*>(w + L.off_rh);
     r.ax = reinterpret_cast<double*>(w + L.off_ax);
     r.part = reinterpret_cast<double*>(w + L.off_part);
@@ -507,9 +581,9 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     r.vec_r = words_ok(rsz, n5, {r.xl}) && words_ok(inner_ == QDWF_F16 ? 2 : rsz, n5, {r.rl}) ? 1 : 0;
     r.vec_b = words_ok(8, n5, {r.b}) ? 1 : 0;
     r.scale = inner_ != QDWF_F64 ? 1 : 0;
-    r.max_iter = m[j].max_iter > 0 ? m[j].max_iter : 20000;
-    r.tol2 = m[j].tol * m[j].tol;
-    const double delta = m[j].delta > 0 ? m[j].delta : 0.1;
+    r.max_iter = mj.max_iter > 0 ? mj.max_iter : 20000;
+    r.tol2 = mj.tol * mj.tol;
+    const double delta = mj.delta > 0 ? mj.delta : 0.1;
     r.delta2 = inner_ == QDWF_F64 ? 0.0 : delta * delta;
     HopK* hs[4] = {&T.hop_s[0][j], &T.hop_s[1][j], &T.hop_s[2][j], &T.hop_s[3][j]};
     GLoc* ls[2] = {&T.loc_s[0][j], &T.loc_s[1][j]};
@@ -523,14 +597,15 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     if ((rc = fill_mdagm(c, QDWF_F64, r.xh, r.ax, w + L.off_vh, w + L.off_t1h, w + L.off_t2h, hd, ld)))
       return rc;
     const int gpw = 64 / g.Ls;
-    T.blas.start[j + 1] = T.blas.start[j] + r.NB;
-    T.sites.start[j + 1] = T.sites.start[j] + r.NBs;
-    T.one.start[j + 1] = j + 1;
+    const int cl = class_of(g.Ls);
+    ClassHdr& C = T.cls[cl];
+    const int i = j - C.first;
     const int hop_units = (g.Vh + 4 * gpw - 1) / (4 * gpw);
-    T.hop16.start[j + 1] = T.hop16.start[j] + (g.Ls == 16 ? hop_units : 0);
-    T.hopg.start[j + 1] = T.hopg.start[j] + (g.Ls == 16 ? 0 : hop_units);
     const int G = (kLocalThreads / 64) * gpw;
-    T.loc.start[j + 1] = T.loc.start[j] + (g.Ls == 16 ? 0 : (g.Vh + G - 1) / G);
+    C.blas.start[i + 1] = C.blas.start[i] + r.NB;
+    C.sites.start[i + 1] = C.sites.start[i] + r.NBs;
+    C.hop.start[i + 1] = C.hop.start[i] + hop_units;
+    C.loc.start[i + 1] = C.loc.start[i] + (cl == CLS_LOCAL ? (g.Vh + G - 1) / G : 0);
   }
   QDWF_HIP(hipMemcpyAsync(table_, staging_, sizeof(Table), hipMemcpyHostToDevice, st));
   return QDWF_OK;
@@ -556,8 +631,34 @@ int GroupEngine::start_member(const GroupMember& m, hipStream_t st) {
   return QDWF_OK;
 }
 
+// The classes' rounds touch disjoint members, so they run side by side: the
+// first one present on the caller's stream, the others on streams of the
+// engine that start after st's earlier work and that st then waits for.
 int GroupEngine::launch_round(hipStream_t st) {
-  QDWF_HIP(hipGraphLaunch(exec_, st));
+  int lead = 0;
+  while (lead < CLS_COUNT && !present_[lead]) ++lead;
+  if (lead == CLS_COUNT) return QDWF_OK;
+  hipError_t err = hipSuccess;
+  auto ok = [&](hipError_t e) {
+    if (err == hipSuccess) err = e;
+    return err == hipSuccess;
+  };
+  bool started[CLS_COUNT] = {};
+  for (int c = lead + 1; c < CLS_COUNT; ++c) {
+    if (!present_[c]) continue;
+    if (!started[lead]) (void)ok(hipEventRecord(fork_, st));
+    started[lead] = true;
+    if (ok(err) && ok(hipStreamWaitEvent(aux_[c], fork_, 0)) && ok(hipGraphLaunch(exec_[c], aux_[c])))
+      started[c] = ok(hipEventRecord(join_[c], aux_[c]));
+  }
+  if (ok(err)) (void)ok(hipGraphLaunch(exec_[lead], st));
+  // whatever was started is waited for, also after an error
+  for (int c = lead + 1; c < CLS_COUNT; ++c)
+    if (started[c]) {
+      const hipError_t e = hipStreamWaitEvent(st, join_[c], 0);
+      if (err == hipSuccess) err = e;
+    }
+  QDWF_HIP(err);
   return QDWF_OK;
 }
 
