@@ -121,12 +121,81 @@ __device__ inline void k_dot_body(const SA* __restrict__ a, const SB* __restrict
   if (threadIdx.x == 0) part[(long)r * NB + bx] = t;
 }
 
-// alpha = rr / <p, Ap>, <p, Ap> = |M_pc p|^2 from the partials; j >= 0:
-// also kept as alpha_hist[j] (iteration j of a group of qdwf_solve)
-__device__ inline void k_alpha_body(const double* __restrict__ part, int NB,
-                                              RhsState* __restrict__ st,
+// Sum of the n values v[q*n ...] the fused CG step leaves (one per wavefront
+// of the hop) in two levels of a fixed order: groups of 1024 values, each by
+// one wavefront (lane l takes values l, l + 64, ...; then the lanes by
+// halves); then the groups' sums the same way by one wavefront. One block
+// does both levels (values_total) up to kOneBlock values; beyond, a
+// launch of many blocks leaves the groups' sums (group_sums_part) and the
+// second level reads those: the same bits either way. One block reads 8192
+// values (16^4 x 16) in about the time of the launch it saves, solve of 256
+// iterations 36.5 -> 35.5 ms; at 41472 (24^4 x 16) it takes twice that and
+// the solve is 1 % slower than with two launches.
+constexpr int ST = 1024;
+constexpr int kGroup = 1024;             // values of a group
+constexpr long kOneBlock = 16384;
+inline int sum_groups(long n) { return (int)((n + kGroup - 1) / kGroup); }
+
+__device__ inline double wave_sum(double t) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) t += __shfl_down(t, d, 64);
+  return t;   // on lane 0
+}
+__device__ inline double group_sum(const double* __restrict__ v, long n, long g) {
+  double a[kGroup / 64], t = 0;
+#pragma unroll
+  for (int k = 0; k < kGroup / 64; ++k) {   // all loads in flight
+    const long i = g * kGroup + k * 64 + (threadIdx.x & 63);
+    a[k] = i < n ? v[i] : 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < kGroup / 64; ++k) t += a[k];
+  return wave_sum(t);
+}
+// second level over the ng groups' sums p (one wavefront)
+__device__ inline double groups_total(const double* p, int ng) {
+  double t = 0;
+  for (int g = threadIdx.x & 63; g < ng; g += 64) t += p[g];
+  return wave_sum(t);
+}
+// part[q*ng + g] = sum of group g (a wavefront per group; blocks of RT threads)
+__device__ inline void group_sums_part(const double* __restrict__ v, long n,
+                                       double* __restrict__ part, int bx, int q) {
+  const int ng = (int)((n + kGroup - 1) / kGroup);
+  const int g = bx * (RT / 64) + (int)(threadIdx.x >> 6);
+  if (g >= ng) return;
+  const double t = group_sum(v + (long)q * n, n, g);
+  if ((threadIdx.x & 63) == 0) part[(long)q * ng + g] = t;
+}
+// Total on thread 0, by one block of ST threads: of the values v themselves
+// (part null), or of their groups' sums. sh: ST doubles.
+__device__ inline double values_total(const double* __restrict__ v, const double* __restrict__ part,
+                                      long n, int q, double* sh) {
+  const int ng = (int)((n + kGroup - 1) / kGroup);
+  if (part) return threadIdx.x < 64 ? groups_total(part + (long)q * ng, ng) : 0.0;
+  const int wave = threadIdx.x >> 6;
+  double run = 0;   // lane l of the first wavefront: groups l, l + 64, ... in order
+  for (int g0 = 0; g0 < ng; g0 += ST) {
+    const int m = min(ST, ng - g0);
+    for (int g = wave; g < m; g += ST / 64) {
+      const double t = group_sum(v + (long)q * n, n, g0 + g);
+      if ((threadIdx.x & 63) == 0) sh[g] = t;
+    }
+    __syncthreads();
+    if (wave == 0)
+      for (int g = threadIdx.x; g < m; g += 64) run += sh[g];
+    __syncthreads();
+  }
+  return wave == 0 ? wave_sum(run) : 0.0;
+}
+
+// alpha = rr / <p, Ap>, <p, Ap> = |M_pc p|^2 from the n sums the hop left
+// (site, or their groups' sums in part); j >= 0: also kept as alpha_hist[j] (iteration j of a group of qdwf_solve)
+__device__ inline void k_alpha_body(const double* __restrict__ site,
+                                    const double* __restrict__ part, long n,
+                                    RhsState* __restrict__ st,
     int q, double* sh, int j = -1) {
-  const double pAp = part_sum(part, NB, q, sh);
+  const double pAp = values_total(site, part, n, q, sh);
   if (threadIdx.x) return;
   RhsState& s = st[q];
   s.fresh = 0;
@@ -142,10 +211,11 @@ __device__ inline void k_alpha_body(const double* __restrict__ part, int NB,
 }
 
 // beta = rr_new / rr ; decide whether a reliable update is due
-__device__ inline void k_beta_body(const double* __restrict__ part, int NB,
-                                             RhsState* __restrict__ st, double delta2,
+__device__ inline void k_beta_body(const double* __restrict__ site,
+                                   const double* __restrict__ part, long n,
+                                   RhsState* __restrict__ st, double delta2,
     int q, double* sh, int j = -1) {
-  const double rr_new = part_sum(part, NB, q, sh);
+  const double rr_new = values_total(site, part, n, q, sh);
   if (threadIdx.x) return;
   RhsState& s = st[q];
   s.xstep = s.status == ST_RUN;
@@ -272,16 +342,6 @@ __device__ inline void k_grp_last_body(SX* __restrict__ x, const SR* __restrict_
       pr[i] = Store<SP>::from(run ? (T)Store<SR>::to(rr[i]) + be * pv : pv);
     }
   }
-}
-
-// part[q*NB + bx] = sum of block bx's share of the n values v[q*n ...]
-__device__ inline void k_sum_body(const double* __restrict__ v, long n, double* __restrict__ part,
-    int bx, int NB, int q, double* sh) {
-  const double* vr = v + (long)q * n;
-  double acc = 0;
-  for (long i = (long)bx * RT + threadIdx.x; i < n; i += (long)NB * RT) acc += vr[i];
-  const double t = block_sum(acc, sh);
-  if (threadIdx.x == 0) part[(long)q * NB + bx] = t;
 }
 
 // ---- reliable update -------------------------------------------------------

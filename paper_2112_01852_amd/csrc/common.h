@@ -250,8 +250,9 @@ struct HopArgs {
   const int* skip;
   int skip_stride;
   // CG step fused into a one-parity hop with epilogue (no minv), for the
-  // solver's M_pc p and M_pc^dag (M_pc p); cg_site[r * Vh + i] receives a
-  // sum of squares over the Ls slices of checkerboard site i of rhs r:
+  // solver's M_pc p and M_pc^dag (M_pc p), one right-hand side per block;
+  // cg_site[r * nw + w], nw = site_waves(Vh, Ls), receives a sum of squares
+  // over the slices of the 64 / Ls checkerboard sites of wavefront w of rhs r:
   //   cg = 1: of the output as stored;
   //   cg = 2: the output is not stored; cg_r -= alpha_r * output instead
   //     (alpha_r = cg_alpha[r * cg_alpha_stride]; cg_r in FP16 for FP16
@@ -272,6 +273,8 @@ struct HopArgs {
   const void* cg_p;
   int chained;   // 1: the caller's next launch reads the output (nt_stores)
 };
+// Wavefronts that hold a right-hand side's half field, 64 / Ls sites each.
+inline int site_waves(int Vh, int Ls) { return (Vh + 64 / Ls - 1) / (64 / Ls); }
 int launch_hop(qdwf_ctx* ctx, int prec, int layout, int dagger, const HopArgs& a,
                hipStream_t st, const HopShape* shape = nullptr);
 

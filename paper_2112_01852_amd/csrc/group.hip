@@ -41,7 +41,7 @@ struct UnitHdr {
 // A class: members [first, first + n) of the table and their units.
 struct ClassHdr {
   int first, n;
-  UnitHdr blas, hop, loc, sites;
+  UnitHdr blas, hop, loc;
 };
 
 // A member's vectors and scalars as the grouped vector kernels see them.
@@ -49,9 +49,8 @@ struct GReq {
   RhsState* st;
   long n;                 // reals of a half field
   int NB;                 // reduction blocks
-  int NBs;                // blocks of the reduction of the per-site sums
-  long nsite;             // checkerboard sites (per-site sums of the fused CG step)
-  double* site;           // per-site sums, written by the fused hops
+  long nw;                // wavefronts of the half field
+  double* site;           // one sum per wavefront, written by the fused hops
   int vec_s, vec_r;       // the inner vectors may be walked in aligned words
   int vec_b;              // the FP64 source may be walked in aligned words
   int scale;              // inner vectors kept at unit RMS (inner precision below FP64)
@@ -175,29 +174,22 @@ g_local(const Table* __restrict__ t, int c, int which, int fp64, int want) {
     const GReq& r = t->req[un.first + j];                     \
     const int bx = u - un.start_of(j);
 
-// The fused iteration's reductions of the per-site sums (|M_pc p|^2, then
-// |r|^2), alpha and beta as in the single-context solver, and the p pass
-// (x takes its step in the last hop of M_pc^dag).
-__global__ void __launch_bounds__(RT) g_sum_sites(const Table* __restrict__ t, int c) {
-  __shared__ double sh[RT];
-  GROUP_LOOP(sites, ST_RUN)
-    k_sum_body(r.site, r.nsite, r.part, bx, r.NBs, 0, sh);
+// The fused iteration's alpha and beta from the hops' sums (|M_pc p|^2, then
+// |r|^2) as in the single-context solver, and the p pass (x takes its step
+// in the last hop of M_pc^dag).
+__global__ void __launch_bounds__(ST) g_alpha(const Table* __restrict__ t, int c) {
+  __shared__ double sh[ST];
+  for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
+    const GReq& r = t->req[t->cls[c].first + j];
+    k_alpha_body(r.site, nullptr, r.nw, r.st, 0, sh);
   }
 }
 
-__global__ void __launch_bounds__(RT) g_alpha(const Table* __restrict__ t, int c) {
-  __shared__ double sh[RT];
+__global__ void __launch_bounds__(ST) g_beta(const Table* __restrict__ t, int c) {
+  __shared__ double sh[ST];
   for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
     const GReq& r = t->req[t->cls[c].first + j];
-    k_alpha_body(r.part, r.NBs, r.st, 0, sh);
-  }
-}
-
-__global__ void __launch_bounds__(RT) g_beta(const Table* __restrict__ t, int c) {
-  __shared__ double sh[RT];
-  for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
-    const GReq& r = t->req[t->cls[c].first + j];
-    k_beta_body(r.part, r.NBs, r.st, r.delta2, 0, sh);
+    k_beta_body(r.site, nullptr, r.nw, r.st, r.delta2, 0, sh);
   }
 }
 
@@ -274,14 +266,12 @@ bool words_ok(size_t elem, long n, std::initializer_list<const void*> ptrs) {
   return true;
 }
 
-// LDS of a grouped hop launch: the largest member's (cg: with the fused CG
-// step's one double per thread)
-size_t hop_lds_max(size_t real_bytes, size_t lstride, bool cg) {
+// LDS of a grouped hop launch: the largest member's
+size_t hop_lds_max(size_t real_bytes, size_t lstride) {
   size_t m = 0;
   for (int Ls = kLsMin; Ls <= kLsMax; ++Ls) {
     const int nsb = 4 * (64 / Ls);
-    m = std::max(m, (size_t)8 * lstride * nsb * real_bytes + (size_t)8 * nsb * sizeof(int) +
-                        (cg ? 256 * sizeof(double) : 0));
+    m = std::max(m, (size_t)8 * lstride * nsb * real_bytes + (size_t)8 * nsb * sizeof(int));
   }
   return m;
 }
@@ -305,8 +295,8 @@ constexpr int kUpdateEvery = 4;
 template <class S, class R, int LAYOUT>
 int record_round(const Table* t, int c, int k, hipStream_t st) {
   typedef typename Store<S>::compute T;
-  const size_t lds_s = hop_lds_max(sizeof(T), LinkStride<T>::v, true);
-  const size_t lds_d = hop_lds_max(sizeof(double), LinkStride<double>::v, false);
+  const size_t lds_s = hop_lds_max(sizeof(T), LinkStride<T>::v);
+  const size_t lds_d = hop_lds_max(sizeof(double), LinkStride<double>::v);
   const size_t loc_s = local_lds_max(sizeof(T));
   const size_t loc_d = local_lds_max(sizeof(double));
   const dim3 hg(kHopGrid), hb(256), lg(kLocalGrid), lb(kLocalThreads), bg(kBlasGrid), bb(RT),
@@ -356,11 +346,9 @@ int record_round(const Table* t, int c, int k, hipStream_t st) {
     // one iteration of the running members, its vector steps fused into
     // the last hops of M_pc and M_pc^dag
     mpc(S(), lds_s, loc_s, 0, ST_RUN);
-    hipLaunchKernelGGL(g_sum_sites, bg, bb, 0, st, t, c);
-    hipLaunchKernelGGL(g_alpha, og, bb, 0, st, t, c);
+    hipLaunchKernelGGL(g_alpha, og, dim3(ST), 0, st, t, c);
     mpc_dag(S(), lds_s, loc_s, 0, ST_RUN);
-    hipLaunchKernelGGL(g_sum_sites, bg, bb, 0, st, t, c);
-    hipLaunchKernelGGL(g_beta, og, bb, 0, st, t, c);
+    hipLaunchKernelGGL(g_beta, og, dim3(ST), 0, st, t, c);
     hipLaunchKernelGGL((g_update_p<S>), bg, bb, 0, st, t, c);
   }
   QDWF_HIP(hipGetLastError());
@@ -546,7 +534,7 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
       if (class_of(m[j].ctx->g.Ls) == c) order[listed++] = j;
     C.n = listed - C.first;
     present_[c] = C.n;
-    C.blas.start[0] = C.hop.start[0] = C.loc.start[0] = C.sites.start[0] = 0;
+    C.blas.start[0] = C.hop.start[0] = C.loc.start[0] = 0;
   }
   const size_t ps = prec_bytes(inner_);
   const size_t rsz = inner_ == QDWF_F64 ? 8 : 4;
@@ -564,9 +552,8 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     r.st = mj.st;
     r.n = n5;
     r.NB = reduce_blocks(n5);
-    r.nsite = g.Vh;
-    r.NBs = site_blocks(g.Vh);
-    // the per-site sums take the room of Ap, which the fused iteration never stores
+    r.nw = site_waves(g.Vh, g.Ls);
+    // the wavefronts' sums take the room of Ap, which the fused iteration never stores
     r.site = reinterpret_cast<double*>(w + L.off_ap);
     r.xl = w + L.off_xl;
     r.rl = w + L.off_rl;
@@ -603,7 +590,6 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     const int hop_units = (g.Vh + 4 * gpw - 1) / (4 * gpw);
     const int G = (kLocalThreads / 64) * gpw;
     C.blas.start[i + 1] = C.blas.start[i] + r.NB;
-    C.sites.start[i + 1] = C.sites.start[i] + r.NBs;
     C.hop.start[i + 1] = C.hop.start[i] + hop_units;
     C.loc.start[i + 1] = C.loc.start[i] + (cl == CLS_LOCAL ? (g.Vh + G - 1) / G : 0);
   }

@@ -112,6 +112,8 @@ int launch_hop(qdwf_ctx* ctx, int prec, int layout, int dagger, const HopArgs& a
   HopShape sh;
   if (shape) sh = *shape;
   else if (!tuned_shape(ctx, prec, layout, dagger, a.nrhs, &sh)) sh = default_shape(ctx, prec, a.nrhs);
+  // the fused CG step sums one right-hand side per wavefront
+  if (a.cg && sh.nrb != 1) sh = default_shape(ctx, prec, a.nrhs);
   const int G = (sh.threads / 64) * (64 / ctx->g.Ls);
   if (sh.threads % 64 || sh.threads < 64 || sh.threads > 256 || sh.nrb < 1 || G % sh.nrb)
     return fail(QDWF_EINVAL, "invalid hop launch shape (threads %d, nrb %d)", sh.threads, sh.nrb);

@@ -50,7 +50,8 @@ struct HopK {
   void* cg_r;
   const double* cg_alpha;
   int cg_alpha_stride;
-  double* cg_site;
+  double* cg_site;     // one sum per wavefront of each rhs
+  int nw;              // wavefronts of a rhs: site_waves(Vh, Ls)
   void* cg_x;          // cg = 3: inner solution, compute type
   const void* cg_p;    // cg = 3: search direction, storage type
   int nt;              // store the output non-temporally (nt_stores)
@@ -437,11 +438,14 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
   }
   if (!MINV && k.cg) {
     // the CG step: this 5D site's sum of squares (components in order), then
-    // each checkerboard site's sum over its slices in slice order (FP64), so
-    // the per-site values do not depend on the launch shape. The site's sum
-    // is taken in FP32 where the values are 16-bit numbers as stored (their
-    // squares are exact in FP32, and 24 of them add with a relative error
-    // below 2^-19), in FP64 otherwise.
+    // the sum over a wavefront's 5D sites by halves (FP64): wavefront w of a
+    // right-hand side always holds checkerboard sites [w gpw, (w + 1) gpw),
+    // so the sums do not depend on the launch shape. A site's sum is taken in
+    // FP32 where the values are 16-bit numbers as stored (their squares are
+    // exact in FP32, and 24 of them add with a relative error below 2^-19),
+    // in FP64 otherwise. One value per wavefront is few enough for the next
+    // launch to add in one block: per checkerboard site it took a reduction
+    // launch more (4.5 us at any size, twice per iteration).
     const bool live = active && (!k.skip || k.skip[(long)rc * k.skip_stride] == 0);
     double ss = 0.0;
     if (k.cg == 1) {
@@ -497,17 +501,13 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
         SiteIO<T, LAYOUT>::store(xr, cbc, s, Ls, k.plane, xv);
       }
     }
-    double* red = reinterpret_cast<double*>(snb + 8 * k.nsb);   // blockDim.x doubles
-    red[threadIdx.x] = live ? ss : 0.0;
-    __syncthreads();
-    if (live && s == 0) {
-      double t = 0.0;
-      for (int j = 0; j < Ls; ++j) t += red[threadIdx.x + j];
-      k.cg_site[(long)rc * Vh + cb] = t;
-    }
+    double t = live ? ss : 0.0;
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) t += __shfl_down(t, d, 64);
+    const int w = sb * (int)(blockDim.x >> 6) + wave;
+    if (lane == 0 && cb0 + wave * k.gpw < Vh) k.cg_site[(long)rc * k.nw + w] = t;
   }
 }
-
 
 // Ls = 2^nd md with md odd: the steps of the fused M_ee^-1.
 inline void minv_steps(int Ls, int* nd, int* md) {
@@ -560,10 +560,11 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
   k->cg_alpha = a.cg_alpha;
   k->cg_alpha_stride = a.cg_alpha_stride;
   k->cg_site = a.cg_site;
+  k->nw = site_waves(g.Vh, g.Ls);
   k->cg_x = a.cg_x;
   k->cg_p = a.cg_p;
   k->nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0);
-  if (a.cg && (a.cg > 3 || !a.epi || a.npar != 1 || !a.cg_site ||
+  if (a.cg && (a.cg > 3 || sh.nrb != 1 || !a.epi || a.npar != 1 || !a.cg_site ||
                (a.cg >= 2 && (!a.cg_r || !a.cg_alpha)) || (a.cg == 3 && (!a.cg_x || !a.cg_p))))
     return fail(QDWF_EINVAL, "fused CG step needs a one-parity hop with epilogue and its buffers");
   k->minv = MINV;
@@ -584,9 +585,9 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
     k->md = 1;
     for (int j = 0; j < 6; ++j) k->rpow[j] = 0.0;
   }
-  // links, neighbour table, then (fused CG step) one double per thread
+  // links, neighbour table
   *lds = (size_t)8 * LinkStride<T>::v * k->nsb * sizeof(T) + (size_t)8 * k->nsb * sizeof(int) +
-         (a.cg ? (size_t)sh.threads * sizeof(double) : 0) + (size_t)sh.lds_pad;
+         (size_t)sh.lds_pad;
   if (*lds > 64 * 1024) return fail(QDWF_EINVAL, "hop launch shape needs %zu bytes of LDS", *lds);
   *nblocks = nsblk * k->nrblk * a.npar;
   return QDWF_OK;

@@ -61,7 +61,6 @@ constexpr int kGroupSlots = 8;
 Layout solver_layout(long n, int nrhs, int inner, bool grouped = false);
 
 int reduce_blocks(long n);
-int site_blocks(long nsite);
 // skip, skip_stride: per right-hand-side flags of the hops (HopArgs::skip);
 // chained: the caller's next launch reads the result (HopArgs::chained)
 int apply_hop_parity(qdwf_ctx* ctx, int prec, int layout, int dagger, int out_par, void* out,

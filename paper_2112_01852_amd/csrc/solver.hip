@@ -43,16 +43,23 @@ __global__ void __launch_bounds__(RT) k_dot(const SA* __restrict__ a, const SB* 
   k_dot_body<SA, SB>(a, b, n, rsa, rsb, part, vec, blockIdx.x, gridDim.x, blockIdx.y, sh);
 }
 
-__global__ void __launch_bounds__(RT) k_alpha(const double* __restrict__ part, int NB,
+__global__ void __launch_bounds__(ST) k_alpha(const double* __restrict__ site,
+                                              const double* __restrict__ part, long nw,
                                               RhsState* __restrict__ st, int j) {
-  __shared__ double sh[RT];
-  k_alpha_body(part, NB, st, blockIdx.x, sh, j);
+  __shared__ double sh[ST];
+  k_alpha_body(site, part, nw, st, blockIdx.x, sh, j);
 }
 
-__global__ void __launch_bounds__(RT) k_beta(const double* __restrict__ part, int NB,
+__global__ void __launch_bounds__(ST) k_beta(const double* __restrict__ site,
+                                             const double* __restrict__ part, long nw,
                                              RhsState* __restrict__ st, double delta2, int j) {
-  __shared__ double sh[RT];
-  k_beta_body(part, NB, st, delta2, blockIdx.x, sh, j);
+  __shared__ double sh[ST];
+  k_beta_body(site, part, nw, st, delta2, blockIdx.x, sh, j);
+}
+
+__global__ void __launch_bounds__(RT) k_group_sums(const double* __restrict__ v, long n,
+                                                   double* __restrict__ part) {
+  group_sums_part(v, n, part, blockIdx.x, blockIdx.y);
 }
 
 template <class SR, class SP>
@@ -67,12 +74,6 @@ __global__ void __launch_bounds__(RT) k_grp_last(SX* __restrict__ x, const SR* _
                                                  SP* __restrict__ p0, long ps, int len, long n,
                                                  const RhsState* __restrict__ st, int vec) {
   k_grp_last_body<SX, SR, SP>(x, r, p0, ps, len, n, n, st, vec, blockIdx.x, gridDim.x, blockIdx.y);
-}
-
-__global__ void __launch_bounds__(RT) k_sum_sites(const double* __restrict__ v, long n,
-                                                  double* __restrict__ part) {
-  __shared__ double sh[RT];
-  k_sum_body(v, n, part, blockIdx.x, gridDim.x, blockIdx.y, sh);
 }
 
 template <class SX>
@@ -166,17 +167,6 @@ __global__ void k_copy64(double* __restrict__ d, const S* __restrict__ s, long n
 }
 
 }  // namespace
-
-// Blocks of the reduction of per-site sums (a few values per thread: the
-// sums are few and the reduction sits between two hops of an iteration).
-// Never more than reduce_blocks gives for the 2 x 24 x Ls x sites reals of
-// the same field, whose partials share the room.
-int site_blocks(long nsite) {
-  long nb = (nsite + 1023) / 1024;
-  if (nb < 1) nb = 1;
-  if (nb > 2048) nb = 2048;
-  return (int)nb;
-}
 
 int reduce_blocks(long n) {
   long nb = (n + 8191) / 8192;
@@ -359,8 +349,10 @@ Layout solver_layout(long n, int nrhs, int inner, bool grouped) {
   L.off_v = o; o += vS;
   L.off_t1 = o; o += vS;
   L.off_t2 = o; o += vS;
-  // partials: room for one reduction over 2n reals per rhs plus 2 results per rhs
-  L.off_part = o; o += al256(sizeof(double) * ((size_t)reduce_blocks(2 * n) * nrhs + 2 * (size_t)nrhs));
+  // partials: room for one reduction over 2n reals per rhs plus 2 results per
+  // rhs, or for the groups' sums of a hop's wavefronts (33 slices each at least)
+  const size_t np = std::max((size_t)reduce_blocks(2 * n), (size_t)sum_groups(n / (24 * 33) + 1));
+  L.off_part = o; o += al256(sizeof(double) * (np * nrhs + 2 * (size_t)nrhs));
   L.off_state = o; o += al256(sizeof(RhsState) * (size_t)nrhs);
   L.off_stage = o; o += al256(8 * (size_t)n * nrhs * 2);   // FULL: source prep / rhs
   L.total = o;
@@ -398,8 +390,8 @@ struct Cg {
   //   r -= alpha M_pc^dag v inside the last hop (Ap is never stored), with
   //   |r|^2 summed there;
   //   beta; p = r + beta p, and x += alpha p once per group of iterations.
-  // The hops leave one sum per checkerboard site (in the room of Ap), which
-  // k_sum_sites reduces with a block count that depends only on the field size.
+  // The hops leave one sum per wavefront (in the room of Ap), which k_alpha
+  // and k_beta add in an order that depends only on the field size.
   // Iterations come in groups of up to kGroupSlots (iteration j of a group
   // of len): iteration j reads p from slot j and writes the next p to slot
   // j + 1; the last one adds every step of the group to x in one pass and
@@ -413,8 +405,7 @@ struct Cg {
     R* x = at<R>(L.off_xl);
     RR* r = at<RR>(L.off_rl);
     double* site = at<double>(L.off_ap);
-    const long nsite = ctx->g.Vh;
-    const int NBs = site_blocks(nsite);
+    const long nw = site_waves(ctx->g.Vh, ctx->g.Ls);
     // the workspace arrays start on 256-byte boundaries and n is a multiple of 24
     const int vec = vec_ok<S>(n, {p0}) && vec_ok<R>(n, {x}) && vec_ok<RR>(n, {r}) ? 1 : 0;
     // the hops of a right-hand side that is not running do no work
@@ -426,16 +417,24 @@ struct Cg {
     if ((rc = apply_mpc(ctx, inner, layout, 0, v, p, at<S>(L.off_t1), at<S>(L.off_t2), nrhs, n, st,
                         skip, sk, &f1)))
       return rc;
-    hipLaunchKernelGGL(k_sum_sites, dim3(NBs, nrhs), dim3(RT), 0, st, site, nsite, part());
-    hipLaunchKernelGGL(k_alpha, dim3(nrhs), dim3(RT), 0, st, part(), NBs, d_state, j);
+    // the hop's sums to one value per rhs: in k_alpha / k_beta alone, or
+    // their groups' sums in a launch before
+    const double* gsum = nw > kOneBlock ? part() : nullptr;
+    auto group_sums = [&] {
+      if (gsum)
+        hipLaunchKernelGGL(k_group_sums, dim3((sum_groups(nw) + RT / 64 - 1) / (RT / 64), nrhs),
+                           dim3(RT), 0, st, site, nw, part());
+    };
+    group_sums();
+    hipLaunchKernelGGL(k_alpha, dim3(nrhs), dim3(ST), 0, st, site, gsum, nw, d_state, j);
     const double* alpha = reinterpret_cast<const double*>(
         reinterpret_cast<const char*>(d_state) + offsetof(RhsState, alpha));
     CgFuse f2 = {2, r, alpha, (int)(sizeof(RhsState) / sizeof(double)), site};
     if ((rc = apply_mpc(ctx, inner, layout, 1, at<S>(L.off_ap), v, at<S>(L.off_t1), at<S>(L.off_t2),
                         nrhs, n, st, skip, sk, &f2)))
       return rc;
-    hipLaunchKernelGGL(k_sum_sites, dim3(NBs, nrhs), dim3(RT), 0, st, site, nsite, part());
-    hipLaunchKernelGGL(k_beta, dim3(nrhs), dim3(RT), 0, st, part(), NBs, d_state, delta2, j);
+    group_sums();
+    hipLaunchKernelGGL(k_beta, dim3(nrhs), dim3(ST), 0, st, site, gsum, nw, d_state, delta2, j);
     if (j + 1 < len)
       hipLaunchKernelGGL((k_grp_p<RR, S>), grid(), dim3(RT), 0, st, r, p0, ps, j, n, d_state, vec);
     else
