@@ -110,6 +110,8 @@ struct HopShape {
   int xcd;       // 1: XCD-aware block order
   int lds_pad;   // extra LDS bytes per block: caps the blocks resident per CU
   int sweep;     // 1: the t-sweep traversal of the full operator where it applies
+  int split = 0; // 1: small launches may give a site's directions to four wavefronts
+                 // (the default shape only: a tuned or given shape is taken as it is)
 };
 
 }  // namespace qdwf

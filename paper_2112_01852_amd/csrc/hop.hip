@@ -30,11 +30,46 @@ hop_kernel(HopK k) {
   hop_block<S, LAYOUT, DAG, DPP16, MINV, CHI>(k, L, smem);
 }
 
+// Small launches in the interleaved layout (hop_block's SPLIT form).
+template <class S, bool DAG, bool DPP16, bool MINV, bool CHI>
+__global__ void __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 1 : 2, sizeof(S) == 8 ? 1 : 2)))
+hop_split_kernel(HopK k) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  hop_block<S, QDWF_RIRI, DAG, DPP16, MINV, CHI, true>(k, blockIdx.x, smem);
+}
+
+// Whether a launch takes the SPLIT form: while four wavefronts for each of
+// the launch's own have room on the chip's 1024 SIMDs at once, at one (FP64)
+// or two per SIMD, and the half spinors fit LDS. us, 256-thread blocks / one
+// wavefront a block / SPLIT: FP64 D 4^4 x 8 12.0 / 9.1 / 8.1 (8 is what the
+// call costs the host), M_pc^dag M_pc FP64 4^4 x 16 36.0 / 27.9 / 25.1, FP32
+// 8^4 x 8 34.7 / 30.7 / 26.4, FP16 8^4 x 16 (512 wavefronts) 27.5 / 25.4 /
+// 24.5; past the line FP64 8^4 x 16 44.4 / 37.4 / 55.2, FP16 D 8^4 x 16 (1024
+// wavefronts) 8.1 / 8.0 / 10.3.
+template <class S> bool split_launch(const qdwf_ctx* ctx, const HopArgs& a) {
+  typedef typename Store<S>::compute T;
+  const int gpw = 64 / ctx->g.Ls;
+  const size_t lds = (size_t)gpw * 8 * (LinkStride<T>::v * sizeof(T) + sizeof(int)) + 16 +
+                     (size_t)6 * 12 * 64 * sizeof(T);
+  return lds <= 64 * 1024 && (long)site_waves(ctx->g.Vh, ctx->g.Ls) * a.npar * a.nrhs <=
+                                 (sizeof(S) == 8 ? 256 : 512);
+}
+
 template <class S, int LAYOUT, bool DAG, bool DPP16, bool MINV, bool CHI>
 int run_hop_k(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st, const HopShape& sh) {
   HopK k;
   size_t lds = 0;
   int nb = 0;
+  if constexpr (LAYOUT == QDWF_RIRI) {
+    if (sh.split && split_launch<S>(ctx, a)) {
+      int rc = make_hopk<S, MINV>(ctx, prec, a, sh, &k, &lds, &nb, true);
+      if (rc) return rc;
+      hipLaunchKernelGGL((hop_split_kernel<S, DAG, DPP16, MINV, CHI>), dim3(nb), dim3(256), lds, st, k);
+      QDWF_HIP(hipGetLastError());
+      return QDWF_OK;
+    }
+  }
   int rc = make_hopk<S, MINV>(ctx, prec, a, sh, &k, &lds, &nb);
   if (rc) return rc;
   // only FP32 in the interleaved layout has a one-parity form of its own;
@@ -75,6 +110,9 @@ int run_hop(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st, const Hop
 
 }  // namespace
 
+// Wavefronts of a launch (of one parity) up to which blocks have one wavefront.
+constexpr long kSmallWaves = 4096;
+
 HopShape default_shape(const qdwf_ctx* ctx, int prec, int nrhs) {
   HopShape sh;
   // at most 32 (site, rhs) groups per block: bounds the LDS link stage
@@ -84,6 +122,12 @@ HopShape default_shape(const qdwf_ctx* ctx, int prec, int nrhs) {
   if (waves < 1) waves = 1;
   if (waves > 4) waves = 4;
   sh.threads = 64 * waves;
+  // small launches in blocks of one wavefront, which reach more CUs: FP64
+  // M_pc^dag M_pc 8^4 x 16 44.4 -> 37.4 us, FP64 D 8^4 x 8 13.9 -> 11.7, FP16
+  // M_pc^dag M_pc 12^4 x 16 44.8 -> 43.0; at 24^4 x 16 (41472 wavefronts of a
+  // parity) they are 2 (FP16) to 7 % (FP64) slower
+  if ((long)site_waves(ctx->g.Vh, ctx->g.Ls) * nrhs <= kSmallWaves) sh.threads = 64;
+  sh.split = 1;
   sh.xcd = 1;
   // one right-hand side per block: with the right-hand sides outermost in the
   // block order this measured faster than sharing the staged links between
@@ -101,9 +145,11 @@ HopShape default_shape(const qdwf_ctx* ctx, int prec, int nrhs) {
   if (const char* e = std::getenv("QDWF_HOP_LDS_PAD")) sh.lds_pad = std::atoi(e);
   if (const char* e = std::getenv("QDWF_HOP_THREADS")) {
     const int t = std::atoi(e);
-    if (t >= 64 && t <= 256 && t % 64 == 0) sh.threads = t;
+    if (t >= 64 && t <= 256 && t % 64 == 0) {
+      sh.threads = t;
+      sh.split = 0;
+    }
   }
-  (void)nrhs;
   return sh;
 }
 

@@ -55,6 +55,7 @@ struct HopK {
   void* cg_x;          // cg = 3: inner solution, compute type
   const void* cg_p;    // cg = 3: search direction, storage type
   int nt;              // store the output non-temporally (nt_stores)
+  int split_off;       // SPLIT: byte offset of the half spinors in LDS
 };
 
 // Target occupancy (waves per SIMD) the register allocator plans for: two for
@@ -95,7 +96,14 @@ __device__ inline void load_link_words(const float* p, uint32_t* U) {
 // and multiplied with v_dot2_f32_f16 into FP32. BF16 storage in that layout
 // projects in FP32 and multiplies with v_dot2_f32_bf16 (no packed BF16 adds
 // on this hardware).
-template <class S, int LAYOUT, bool DAG, bool DPP16, bool MINV, bool CHI = false>
+//
+// SPLIT (small launches): the four wavefronts of a block hold the same 64 / Ls
+// sites, wavefront mu the two hops of direction mu; their partial sums meet
+// in LDS and the first one carries on. A launch of fewer wavefronts than the
+// chip has SIMDs takes as long as one wavefront does, and that is the latency
+// of its loads: a lane alone waits for four pairs of neighbours one after
+// another. (split_launch)
+template <class S, int LAYOUT, bool DAG, bool DPP16, bool MINV, bool CHI = false, bool SPLIT = false>
 __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
   typedef typename Store<S>::compute T;
   static_assert(!(DAG && CHI), "the adjoint hop applies A^dag once per site");
@@ -142,7 +150,9 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
   __syncthreads();
 
   const int Ls = DPP16 ? 16 : k.Ls;   // a constant on the Ls = 16 path
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int mu0 = SPLIT ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+  const int wave = SPLIT ? 0 : (int)(threadIdx.x >> 6);   // among the wavefronts of the block's sites
   const int gl = lane / Ls, s = lane - gl * Ls;
   const bool lane_ok = gl < k.gpw;
   const int gid = wave * k.gpw + (lane_ok ? gl : 0);
@@ -170,12 +180,14 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
       w[2 * c + 1] = qq.y;
     }
   };
+  // (SPLIT: the wavefront's only two)
+  const int n0 = SPLIT ? nbs[mu0 * k.nsb] : nbs[0], n1 = SPLIT ? nbs[(mu0 + 4) * k.nsb] : nbs[k.nsb];
   if constexpr (PK) {
-    load_pk(nbs[0], wa);
-    load_pk(nbs[k.nsb], wb);
+    load_pk(n0, wa);
+    load_pk(n1, wb);
   } else {
-    SiteIO<S, LAYOUT>::load(in, nbs[0], s, Ls, k.plane, va);
-    SiteIO<S, LAYOUT>::load(in, nbs[k.nsb], s, Ls, k.plane, vb);
+    SiteIO<S, LAYOUT>::load(in, n0, s, Ls, k.plane, va);
+    SiteIO<S, LAYOUT>::load(in, n1, s, Ls, k.plane, vb);
   }
 
   {
@@ -228,7 +240,8 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
   T acc[24];
   // direction D uses the buffer loaded two steps earlier and refills it with
   // direction D + 2
-  auto step = [&](auto Dc) {
+  // (the link times the projected neighbour; its spin rows go into uh)
+  auto hop_half = [&](auto Dc, T* uh) __attribute__((always_inline)) {
     constexpr int D = decltype(Dc)::value;
     constexpr int MU = D & 3;
     constexpr bool FWD = D < 4;
@@ -238,13 +251,12 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
     // unless the input already holds it (CHI without MINV) or the hop is the
     // adjoint's
     constexpr bool APPLY_A = !DAG && !(CHI && !MINV);
-    T uh[12];
     if constexpr (PK) {
-      uint32_t* buf = (D & 1) ? wb : wa;
+      uint32_t* buf = (SPLIT ? !FWD : (D & 1)) ? wb : wa;
       uint32_t w[12];
 #pragma unroll
       for (int i = 0; i < 12; ++i) w[i] = buf[i];
-      if constexpr (D < 6) load_pk(nbs[(D + 2) * k.nsb], buf);
+      if constexpr (!SPLIT && D < 6) load_pk(nbs[(D + 2) * k.nsb], buf);
       uint32_t h[6];
       if constexpr (APPLY_A) {
         // chi / b = psi + (c/b) (P+ psi_{s-1} + P- psi_{s+1}) in packed FP16:
@@ -270,11 +282,11 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
       load_link_words(lks + D * LSTR, U);
       su3_mul_pk<!FWD>(U, U + 9, h, uh);
     } else {
-      T* buf = (D & 1) ? vb : va;
+      T* buf = (SPLIT ? !FWD : (D & 1)) ? vb : va;
       T v[24];
 #pragma unroll
       for (int i = 0; i < 24; ++i) v[i] = buf[i];
-      if constexpr (D < 6)
+      if constexpr (!SPLIT && D < 6)
         SiteIO<S, LAYOUT>::load(in, nbs[(D + 2) * k.nsb], s, Ls, k.plane, buf);
       if constexpr (APPLY_A) {
         T w[24];
@@ -297,10 +309,52 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
         su3_mul<!FWD>(U, h, uh);
       }
     }
-    recon_acc<MU, SG, D == 0>(uh, acc);
   };
-  step(IC<0>()); step(IC<1>()); step(IC<2>()); step(IC<3>());
-  step(IC<4>()); step(IC<5>()); step(IC<6>()); step(IC<7>());
+  auto recon = [&](auto Dc, const T* uh) __attribute__((always_inline)) {
+    constexpr int D = decltype(Dc)::value;
+    constexpr int SG = ((D < 4) != DAG) ? -1 : +1;
+    recon_acc<(D & 3), SG, D == 0>(uh, acc);
+  };
+  if constexpr (SPLIT) {
+    T uf[12], ub[12];
+    switch (mu0) {
+      case 0: hop_half(IC<0>(), uf); hop_half(IC<4>(), ub); break;
+      case 1: hop_half(IC<1>(), uf); hop_half(IC<5>(), ub); break;
+      case 2: hop_half(IC<2>(), uf); hop_half(IC<6>(), ub); break;
+      default: hop_half(IC<3>(), uf); hop_half(IC<7>(), ub); break;
+    }
+    // [6][12][64] half spinors behind the links and neighbour indices: the
+    // forward and backward ones of mu = 1, 2, 3. The first wavefront adds all
+    // eight in the order of the other form, so the two agree bit for bit.
+    T* part = reinterpret_cast<T*>(smem + k.split_off) + lane;
+    if (mu0 != 0) {
+      T* o = part + (mu0 - 1) * 2 * 12 * 64;
+#pragma unroll
+      for (int i = 0; i < 12; ++i) {
+        o[i * 64] = uf[i];
+        o[(12 + i) * 64] = ub[i];
+      }
+    }
+    __syncthreads();
+    if (mu0 != 0) return;   // no barrier below
+    auto add = [&](auto Dc) __attribute__((always_inline)) {
+      constexpr int D = decltype(Dc)::value;
+      T uh[12];
+#pragma unroll
+      for (int i = 0; i < 12; ++i) uh[i] = part[((((D & 3) - 1) * 2 + (D >> 2)) * 12 + i) * 64];
+      recon(Dc, uh);
+    };
+    recon(IC<0>(), uf); add(IC<1>()); add(IC<2>()); add(IC<3>());
+    recon(IC<4>(), ub); add(IC<5>()); add(IC<6>()); add(IC<7>());
+  } else {
+    auto step = [&](auto Dc) __attribute__((always_inline)) {
+      T uh[12];
+      hop_half(Dc, uh);
+      recon(Dc, uh);
+    };
+    step(IC<0>()); step(IC<1>()); step(IC<2>()); step(IC<3>());
+    step(IC<4>()); step(IC<5>()); step(IC<6>()); step(IC<7>());
+  }
 
   if constexpr (DAG) {
     // A^dag h / b = h + (c/b) C^dag h, C^dag = P- S_d + P+ S_u:
@@ -504,7 +558,7 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
     double t = live ? ss : 0.0;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1) t += __shfl_down(t, d, 64);
-    const int w = sb * (int)(blockDim.x >> 6) + wave;
+    const int w = SPLIT ? sb : sb * (int)(blockDim.x >> 6) + wave;
     if (lane == 0 && cb0 + wave * k.gpw < Vh) k.cg_site[(long)rc * k.nw + w] = t;
   }
 }
@@ -531,9 +585,10 @@ inline bool minv_fused(int Ls) {
 // Kernel arguments of a hop launch on one context (HopArgs as for
 // launch_hop, the launch shape sh), its LDS bytes per block and its number of
 // logical blocks. MINV: M_ee^-1 fused (minv_fused).
+// split: for hop_block's SPLIT form (256 threads, one right-hand side per block).
 template <class S, bool MINV>
 int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& sh, HopK* k,
-              size_t* lds, int* nblocks) {
+              size_t* lds, int* nblocks, bool split = false) {
   typedef typename Store<S>::compute T;
   const Geom& g = ctx->g;
   for (int i = 0; i < 2; ++i) { k->in[i] = a.in[i]; k->out[i] = a.out[i]; k->z[i] = a.z[i]; }
@@ -543,9 +598,9 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
   k->plane = g.n5h;
   k->Vh = g.Vh; k->Ls = g.Ls; k->nrhs = a.nrhs; k->par0 = a.par0; k->npar = a.npar;
   k->gpw = 64 / g.Ls;
-  const int G = (sh.threads / 64) * k->gpw;
-  k->nrb = sh.nrb;
-  k->nsb = G / sh.nrb;
+  const int G = split ? k->gpw : (sh.threads / 64) * k->gpw;
+  k->nrb = split ? 1 : sh.nrb;
+  k->nsb = G / k->nrb;
   k->nrblk = (a.nrhs + k->nrb - 1) / k->nrb;
   const int nsblk = (g.Vh + k->nsb - 1) / k->nsb;
   k->epi = a.epi; k->xcd = sh.xcd;
@@ -564,7 +619,7 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
   k->cg_x = a.cg_x;
   k->cg_p = a.cg_p;
   k->nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0);
-  if (a.cg && (a.cg > 3 || sh.nrb != 1 || !a.epi || a.npar != 1 || !a.cg_site ||
+  if (a.cg && (a.cg > 3 || k->nrb != 1 || !a.epi || a.npar != 1 || !a.cg_site ||
                (a.cg >= 2 && (!a.cg_r || !a.cg_alpha)) || (a.cg == 3 && (!a.cg_x || !a.cg_p))))
     return fail(QDWF_EINVAL, "fused CG step needs a one-parity hop with epilogue and its buffers");
   k->minv = MINV;
@@ -588,6 +643,11 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
   // links, neighbour table
   *lds = (size_t)8 * LinkStride<T>::v * k->nsb * sizeof(T) + (size_t)8 * k->nsb * sizeof(int) +
          (size_t)sh.lds_pad;
+  k->split_off = 0;
+  if (split) {
+    k->split_off = (int)((*lds + 15) & ~(size_t)15);
+    *lds = k->split_off + (size_t)6 * 12 * 64 * sizeof(T);
+  }
   if (*lds > 64 * 1024) return fail(QDWF_EINVAL, "hop launch shape needs %zu bytes of LDS", *lds);
   *nblocks = nsblk * k->nrblk * a.npar;
   return QDWF_OK;
