@@ -242,6 +242,7 @@ struct HopArgs {
   int minv;   // 1: apply M_ee^-1 (M_ee^-dag when dagger) to the result; epi = 0, minv_fused(Ls)
   int chi;    // D_h only (dagger = 0): without minv, in holds (A/b) in, which the hop
               // takes as it is; with minv, the result is multiplied by A/b
+              // (launch_hop sets it where c = 0, A/b = 1)
   double hop_scale, alpha, beta;
   const void* links;   // links to use instead of the context's (nullptr: the context's)
   // nullptr, or one int per right-hand side (at skip[r * skip_stride]): a

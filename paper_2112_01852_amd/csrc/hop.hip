@@ -10,19 +10,20 @@ namespace qdwf {
 
 namespace {
 
-// Waves per SIMD of a launch: the one-parity hops (D_eo and the solver's
-// M_pc stages) in FP32 with the interleaved layout run at three (132-138
-// registers, no spills), which measured 2-4 % faster than two; the full
-// operator over both parities keeps two, at three it measured 5 % slower.
-template <class S, int LAYOUT, bool DPP16, bool ONEPAR> struct HopWaves {
-  static constexpr int v = (std::is_same<S, float>::value && LAYOUT == QDWF_RIRI && ONEPAR)
+// Waves per SIMD of a launch: FP32 in the interleaved layout runs at three
+// (129-138 registers, no spills), which measured faster than two for the
+// one-parity hops (2-4 %) and, since outputs are stored non-temporally, for
+// the full operator too (D 16^3x32 x 8 93.0 -> 86.2 us, 16^4 x 12 73.0 ->
+// 65.3, 24^4 x 16 355 -> 349; D^dag 84.1 -> 80.2, 63.6 -> 59.8, 349 -> 342).
+template <class S, int LAYOUT, bool DPP16> struct HopWaves {
+  static constexpr int v = (std::is_same<S, float>::value && LAYOUT == QDWF_RIRI)
                                ? 3 : WavesPerEU<S, LAYOUT, DPP16>::v;
 };
 
-template <class S, int LAYOUT, bool DAG, bool DPP16, bool MINV, bool CHI, bool ONEPAR>
+template <class S, int LAYOUT, bool DAG, bool DPP16, bool MINV, bool CHI>
 __global__ void __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(HopWaves<S, LAYOUT, DPP16, ONEPAR>::v,
-                                   HopWaves<S, LAYOUT, DPP16, ONEPAR>::v)))
+__attribute__((amdgpu_waves_per_eu(HopWaves<S, LAYOUT, DPP16>::v,
+                                   HopWaves<S, LAYOUT, DPP16>::v)))
 hop_kernel(HopK k) {
   extern __shared__ __align__(16) unsigned char smem[];
   // the XCD remap hands each XCD a contiguous range of logical blocks
@@ -72,19 +73,8 @@ int run_hop_k(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st, const H
   }
   int rc = make_hopk<S, MINV>(ctx, prec, a, sh, &k, &lds, &nb);
   if (rc) return rc;
-  // only FP32 in the interleaved layout has a one-parity form of its own;
-  // M_ee^-1 and chi hops are one-parity by construction
-  if constexpr (std::is_same<S, float>::value && LAYOUT == QDWF_RIRI) {
-    if (MINV || CHI || a.npar == 1)
-      hipLaunchKernelGGL((hop_kernel<S, LAYOUT, DAG, DPP16, MINV, CHI, true>), dim3(nb),
-                         dim3(sh.threads), lds, st, k);
-    else if constexpr (!MINV && !CHI)
-      hipLaunchKernelGGL((hop_kernel<S, LAYOUT, DAG, DPP16, MINV, CHI, false>), dim3(nb),
-                         dim3(sh.threads), lds, st, k);
-  } else {
-    hipLaunchKernelGGL((hop_kernel<S, LAYOUT, DAG, DPP16, MINV, CHI, false>), dim3(nb),
-                       dim3(sh.threads), lds, st, k);
-  }
+  hipLaunchKernelGGL((hop_kernel<S, LAYOUT, DAG, DPP16, MINV, CHI>), dim3(nb), dim3(sh.threads), lds,
+                     st, k);
   QDWF_HIP(hipGetLastError());
   return QDWF_OK;
 }
@@ -153,8 +143,14 @@ HopShape default_shape(const qdwf_ctx* ctx, int prec, int nrhs) {
   return sh;
 }
 
-int launch_hop(qdwf_ctx* ctx, int prec, int layout, int dagger, const HopArgs& a,
+int launch_hop(qdwf_ctx* ctx, int prec, int layout, int dagger, const HopArgs& a0,
                hipStream_t st, const HopShape* shape) {
+  HopArgs a = a0;
+  // Shamir (c = 0): A/b = 1, so every input is its own chi and no neighbour
+  // goes through the s +- 1 exchange (us: D FP64 16^3x32 x 8 180 -> 166, FP32
+  // 93 -> 79, FP16 54 -> 42; M_pc^dag M_pc FP64 16^4 x 8 193 -> 184)
+  if (!dagger && ctx->act.c == 0.0) a.chi = a.minv ? 0 : 1;
+  else if (!dagger && a.minv && !a.chi) return fail(QDWF_EINVAL, "fused M_ee^-1 hands on A/b times its result");
   HopShape sh;
   if (shape) sh = *shape;
   else if (!tuned_shape(ctx, prec, layout, dagger, a.nrhs, &sh)) sh = default_shape(ctx, prec, a.nrhs);

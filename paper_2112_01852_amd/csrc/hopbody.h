@@ -60,11 +60,13 @@ struct HopK {
 
 // Target occupancy (waves per SIMD) the register allocator plans for: two for
 // 32- and 64-bit storage, whose arithmetic needs the registers to keep two
-// directions' neighbour loads in flight (the one-parity FP32 launches of
-// hop.hip take three instead); four for the packed FP16 path
+// directions' neighbour loads in flight (the FP32 launches of hop.hip take
+// three instead); four for the packed FP16 path
 // (interleaved layout, Ls = 16: neighbour spinors stay packed, 105-114
-// registers, no spills), three for other 16-bit storage (which spills at
-// four).
+// registers, no spills), three for other 16-bit storage (BF16 at four: D
+// 24^4 x 16 273 -> 277 us, D^dag 263 -> 272; the FP16 permute form spills 2-5
+// registers at four, D 16^3x32 x 12 92.9 -> 89.6 but the solve at 12^4 x 12
+// 16.04 -> 16.18 ms).
 template <class S, int LAYOUT = QDWF_RRII, bool DPP16 = false> struct WavesPerEU {
   static constexpr int v =
       sizeof(S) >= 4 ? 2 : (std::is_same<S, _Float16>::value && LAYOUT == QDWF_RIRI && DPP16) ? 4 : 3;
@@ -90,7 +92,8 @@ __device__ inline void load_link_words(const float* p, uint32_t* U) {
 // CHI (D_h only, not the adjoint): without MINV the input already holds
 // chi = (A/b) psi, so the hop takes it as it is; with MINV the result is
 // multiplied by A/b after M_ee^-1 (the two commute: both are functions of
-// C), so that the next hop of M_pc can take it as chi.
+// C), so that the next hop of M_pc can take it as chi. MINV without CHI is
+// for c = 0 (Shamir), where A/b = 1: nothing is applied before or after.
 // FP16 storage in the interleaved layout takes the packed path (pk16.h):
 // neighbour spinors stay packed, half spinors are projected in packed FP16
 // and multiplied with v_dot2_f32_f16 into FP32. BF16 storage in that layout
@@ -248,9 +251,9 @@ __device__ inline void hop_block(const HopK& k, int L, unsigned char* smem) {
     // (1 - g) on forward hops and (1 + g) on backward ones; swapped for D_h^dag
     constexpr int SG = (FWD != DAG) ? -1 : +1;
     // chi / b = psi + (c/b) (P+ psi_{s-1} + P- psi_{s+1}), walls included,
-    // unless the input already holds it (CHI without MINV) or the hop is the
-    // adjoint's
-    constexpr bool APPLY_A = !DAG && !(CHI && !MINV);
+    // unless the input already holds it (CHI without MINV, and always where
+    // c = 0) or the hop is the adjoint's
+    constexpr bool APPLY_A = !DAG && CHI == MINV;
     if constexpr (PK) {
       uint32_t* buf = (SPLIT ? !FWD : (D & 1)) ? wb : wa;
       uint32_t w[12];
