@@ -92,15 +92,13 @@ int launch_local(qdwf_ctx* ctx, int prec, int layout, MatKind kind, void* out, c
     typedef typename Store<S>::compute T;
     // largest block (<= 256 threads) whose staged columns fit in 48 KB of LDS
     int threads = 256;
-    while (threads > 64 &&
-           ((size_t)(threads / 64) * (64 / g.Ls) * g.Ls * 24 + 2 * g.Ls * g.Ls) * sizeof(T) > 48 * 1024)
-      threads /= 2;
+    while (threads > 64 && local_lds_bytes(threads, g.Ls, sizeof(T)) > 48 * 1024) threads /= 2;
     const int G = (threads / 64) * (64 / g.Ls);
     dim3 grid((g.Vh + G - 1) / G, nhalf * nrhs), block(threads);
     const T* K;
     if (sizeof(T) == 8) K = reinterpret_cast<const T*>(ctx->d_mat64 + (size_t)kind * 2 * g.Ls * g.Ls);
     else K = reinterpret_cast<const T*>(ctx->d_mat32 + (size_t)kind * 2 * g.Ls * g.Ls);
-    const size_t lds = ((size_t)G * g.Ls * 24 + 2 * g.Ls * g.Ls) * sizeof(T);
+    const size_t lds = local_lds_bytes(threads, g.Ls, sizeof(T));
     if (layout == QDWF_RIRI)
       hipLaunchKernelGGL((local_kernel<S, QDWF_RIRI>), grid, block, lds, st,
                          reinterpret_cast<const S*>(in), reinterpret_cast<S*>(out), K, g.Vh, g.Ls,
