@@ -343,11 +343,13 @@ int qdwf_traversal(qdwf_ctx* ctx, int32_t* order6);
  * with its own lattice, action, gauge field and source. Requests wait in FIFO
  * order until their device memory (qdwf_request_bytes) fits the caller's
  * arena and one of max_slots slots is free. All admitted requests advance
- * together: each qdwf_pool_step replays one round -- check_every repetitions
- * of [the reliable updates that are due; one CG iteration] -- in which every
- * step of the iteration is a single launch covering all of them (kernels walk
- * a device table of the requests' arguments), captured as a HIP graph when
- * the pool is created. A request's result does not depend on what else is
+ * together: each qdwf_pool_step replays one round -- check_every CG
+ * iterations, with the reliable updates that are due offered every fourth --
+ * in which every step of the iteration is one launch per class of requests
+ * (Ls = 16; other Ls = 2^n m with m <= 5; the rest) covering all of them
+ * (kernels walk a device table of the requests' arguments), captured as HIP
+ * graphs when the pool is created. The classes present run side by side: the
+ * step's stream waits for the pool's own streams that help it. A request's result does not depend on what else is
  * in the pool: its arithmetic is that of qdwf_solve on one right-hand side
  * with the same parameters.
  *

@@ -1,6 +1,7 @@
 // Grouped CG: the even-odd normal-equation solves of many independent
 // requests (each its own lattice, Ls, mass, gauge field and source) advanced
-// together, one launch per step of the iteration for all of them. The serving
+// together, one launch per step of the iteration for each class of them (the
+// forms of the hop, group.hip), the classes side by side. The serving
 // pool's engine.
 //
 // A group keeps, in device memory the caller provides, a descriptor table:
@@ -14,9 +15,9 @@
 // Each request's arithmetic is that of qdwf_solve on one right-hand side
 // with the same parameters: the same kernel bodies (hopbody.h, localbody.h,
 // cgbody.h), its own reduction tree, and the same sequence of iterations and
-// reliable updates. A round is `k` repetitions of [reliable update for the
-// requests that asked for one; one iteration for the running ones], each
-// step skipping the requests it does not apply to. Results are therefore
+// reliable updates. A round is `k` iterations of the running requests, with a
+// reliable update for those that asked for one before every fourth; each
+// step skips the requests it does not apply to. Results are therefore
 // independent of what else is in the group.
 #pragma once
 
