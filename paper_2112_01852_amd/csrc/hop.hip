@@ -42,17 +42,18 @@ hop_split_kernel(HopK k) {
 
 // Whether a launch takes the SPLIT form: while four wavefronts for each of
 // the launch's own have room on the chip's 1024 SIMDs at once, at one (FP64)
-// or two per SIMD, and the half spinors fit LDS. us, 256-thread blocks / one
-// wavefront a block / SPLIT: FP64 D 4^4 x 8 12.0 / 9.1 / 8.1 (8 is what the
-// call costs the host), M_pc^dag M_pc FP64 4^4 x 16 36.0 / 27.9 / 25.1, FP32
-// 8^4 x 8 34.7 / 30.7 / 26.4, FP16 8^4 x 16 (512 wavefronts) 27.5 / 25.4 /
-// 24.5; past the line FP64 8^4 x 16 44.4 / 37.4 / 55.2, FP16 D 8^4 x 16 (1024
-// wavefronts) 8.1 / 8.0 / 10.3.
-template <class S> bool split_launch(const qdwf_ctx* ctx, const HopArgs& a) {
+// or two per SIMD, and the half spinors fit LDS beside the shape's padding.
+// us, 256-thread blocks / one wavefront a block / SPLIT: FP64 D 4^4 x 8 12.0 /
+// 9.1 / 8.1 (8 is what the call costs the host), M_pc^dag M_pc FP64 4^4 x 16
+// 36.0 / 27.9 / 25.1, FP32 8^4 x 8 34.7 / 30.7 / 26.4, FP16 8^4 x 16 (512
+// wavefronts) 27.5 / 25.4 / 24.5; past the line FP64 8^4 x 16 44.4 / 37.4 /
+// 55.2, FP16 D 8^4 x 16 (1024 wavefronts) 8.1 / 8.0 / 10.3.
+template <class S> bool split_launch(const qdwf_ctx* ctx, const HopArgs& a, const HopShape& sh) {
+  if (!sh.split) return false;
   typedef typename Store<S>::compute T;
   const int gpw = 64 / ctx->g.Ls;
   const size_t lds = (size_t)gpw * 8 * (LinkStride<T>::v * sizeof(T) + sizeof(int)) + 16 +
-                     (size_t)6 * 12 * 64 * sizeof(T);
+                     (size_t)sh.lds_pad + (size_t)6 * 12 * 64 * sizeof(T);
   return lds <= 64 * 1024 && (long)site_waves(ctx->g.Vh, ctx->g.Ls) * a.npar * a.nrhs <=
                                  (sizeof(S) == 8 ? 256 : 512);
 }
@@ -63,7 +64,7 @@ int run_hop_k(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st, const H
   size_t lds = 0;
   int nb = 0;
   if constexpr (LAYOUT == QDWF_RIRI) {
-    if (sh.split && split_launch<S>(ctx, a)) {
+    if (split_launch<S>(ctx, a, sh)) {
       int rc = make_hopk<S, MINV>(ctx, prec, a, sh, &k, &lds, &nb, true);
       if (rc) return rc;
       hipLaunchKernelGGL((hop_split_kernel<S, DAG, DPP16, MINV, CHI>), dim3(nb), dim3(256), lds, st, k);
