@@ -111,7 +111,7 @@ struct HopShape {
   int lds_pad;   // extra LDS bytes per block: caps the blocks resident per CU
   int sweep;     // 1: the t-sweep traversal of the full operator where it applies
   int split = 0; // 1: small launches may give a site's directions to four wavefronts
-                 // (the default shape only: a tuned or given shape is taken as it is)
+                 // (hop_splits; the tuner stores which form it found the faster)
 };
 
 }  // namespace qdwf
@@ -280,6 +280,8 @@ struct HopArgs {
 inline int site_waves(int Vh, int Ls) { return (Vh + 64 / Ls - 1) / (64 / Ls); }
 int launch_hop(qdwf_ctx* ctx, int prec, int layout, int dagger, const HopArgs& a,
                hipStream_t st, const HopShape* shape = nullptr);
+// Whether that launch takes the split form (HopShape::split).
+bool hop_splits(const qdwf_ctx* ctx, int prec, int layout, const HopArgs& a, const HopShape& shape);
 
 // t-sweep traversal of the full operator (both parities, epi, z = the input
 // itself, no fused M_ee^-1, the context's links): Ls = 16, interleaved

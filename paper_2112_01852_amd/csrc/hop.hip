@@ -104,6 +104,16 @@ int run_hop(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st, const Hop
 // Wavefronts of a launch (of one parity) up to which blocks have one wavefront.
 constexpr long kSmallWaves = 4096;
 
+bool hop_splits(const qdwf_ctx* ctx, int prec, int layout, const HopArgs& a, const HopShape& sh) {
+  if (layout != QDWF_RIRI) return false;
+  switch (prec) {
+    case QDWF_F64: return split_launch<double>(ctx, a, sh);
+    case QDWF_F32: return split_launch<float>(ctx, a, sh);
+    case QDWF_F16: return split_launch<_Float16>(ctx, a, sh);
+  }
+  return split_launch<bf16>(ctx, a, sh);
+}
+
 HopShape default_shape(const qdwf_ctx* ctx, int prec, int nrhs) {
   HopShape sh;
   // at most 32 (site, rhs) groups per block: bounds the LDS link stage

@@ -5,10 +5,13 @@
 // candidate shape -- threads per block, right-hand sides per block, XCD-aware
 // block order on/off, and an LDS reservation that caps how many blocks share
 // a CU -- is timed with HIP events on the full operator D and on D^dag, and
-// the fastest is kept in the context. With QDWF_TUNE_CACHE naming a file, the
-// results are appended there (one JSON object per line, keyed by lattice, Ls,
-// precision, layout, dagger, nrhs and device architecture) and read back when
-// a context of the same shape is created, so tuning happens once per machine.
+// the fastest is kept in the context, unless the shape of an untuned call,
+// timed once more beside it on the full operator and on a one-parity hop
+// (which a tuned shape serves too), turns out no slower. With
+// QDWF_TUNE_CACHE naming a file, the results are appended there (one JSON
+// object per line, keyed by lattice, Ls, precision, layout, dagger, nrhs and
+// device architecture) and read back when a context of the same shape is
+// created, so tuning happens once per machine.
 //
 // The traversal order (split and sweep dimension, tile) is fixed when a
 // context is created, since the links and every packed field follow it, and
@@ -61,8 +64,8 @@ void cache_store(const std::string& key, const HopShape& s, double ms) {
   if (!path || !*path) return;
   FILE* f = std::fopen(path, "a");
   if (!f) return;
-  std::fprintf(f, "{\"key\": \"%s\", \"threads\": %d, \"nrb\": %d, \"xcd\": %d, \"lds_pad\": %d, \"sweep\": %d, \"ms\": %.6f}\n",
-               key.c_str(), s.threads, s.nrb, s.xcd, s.lds_pad, s.sweep, ms);
+  std::fprintf(f, "{\"key\": \"%s\", \"threads\": %d, \"nrb\": %d, \"xcd\": %d, \"lds_pad\": %d, \"sweep\": %d, \"split\": %d, \"ms\": %.6f}\n",
+               key.c_str(), s.threads, s.nrb, s.xcd, s.lds_pad, s.sweep, s.split, ms);
   std::fclose(f);
 }
 
@@ -76,10 +79,13 @@ bool cache_load(const std::string& key, HopShape* out) {
   while (std::fgets(line, sizeof(line), f)) {
     char k[256];
     HopShape s;
-    double ms;
-    if (std::sscanf(line, "{\"key\": \"%255[^\"]\", \"threads\": %d, \"nrb\": %d, \"xcd\": %d, \"lds_pad\": %d, \"sweep\": %d, \"ms\": %lf}",
-                    k, &s.threads, &s.nrb, &s.xcd, &s.lds_pad, &s.sweep, &ms) == 7 &&
+    int at = 0;
+    if (std::sscanf(line, "{\"key\": \"%255[^\"]\", \"threads\": %d, \"nrb\": %d, \"xcd\": %d, \"lds_pad\": %d, \"sweep\": %d, %n",
+                    k, &s.threads, &s.nrb, &s.xcd, &s.lds_pad, &s.sweep, &at) == 6 && at &&
         key == k) {
+      // a line without "split" chose between shapes of the ordinary form only:
+      // small launches keep theirs, as an untuned call's do
+      if (std::sscanf(line + at, "\"split\": %d", &s.split) != 1) s.split = 1;
       *out = s;   // the last entry for a key wins
       found = true;
     }
@@ -247,31 +253,51 @@ int qdwf_tune(qdwf_ctx* ctx, int prec, int layout, int nrhs, void* ws, void* str
   QDWF_HIP(hipEventCreate(&e0));
   QDWF_HIP(hipEventCreate(&e1));
   const int gpw = 64 / ctx->g.Ls;
-  const int reps = 5;
+  int reps = 5;
+  // *ms = a launch of h in shape s; 1e30 if the kernel rejects the shape (LDS)
+  auto timed = [&](const HopArgs& h, int dagger, const HopShape& s, double* ms) -> int {
+    *ms = 1e30;
+    if (launch_hop(ctx, prec, layout, dagger, h, st, &s) != QDWF_OK) return QDWF_OK;   // warm-up
+    QDWF_HIP(hipEventRecord(e0, st));
+    for (int r = 0; r < reps; ++r) launch_hop(ctx, prec, layout, dagger, h, st, &s);
+    QDWF_HIP(hipEventRecord(e1, st));
+    QDWF_HIP(hipEventSynchronize(e1));
+    float t = 0;
+    QDWF_HIP(hipEventElapsedTime(&t, e0, e1));
+    *ms = t / reps;
+    return QDWF_OK;
+  };
+  HopArgs one = a;   // a hop to one parity
+  one.npar = 1;
   for (int dagger = 0; dagger < 2; ++dagger) {
-    HopShape best = default_shape(ctx, prec, nrhs);
-    double best_t = 1e30;
+    const HopShape untuned = default_shape(ctx, prec, nrhs);
+    HopShape best = untuned;
+    best.sweep = 0;
+    double best_t = 0, t = 0;
+    reps = 5;
+    if (int rc = timed(a, dagger, best, &best_t)) return rc;
+    // short launches often enough for half a millisecond
+    reps = std::max(5, (int)std::min(50.0, 0.5 / std::max(best_t, 1e-3)));
+    if (int rc = timed(a, dagger, best, &best_t)) return rc;
+    auto attempt = [&](const HopShape& s) -> int {
+      if (int rc = timed(a, dagger, s, &t)) return rc;
+      if (t < best_t) {
+        best_t = t;
+        best = s;
+      }
+      return QDWF_OK;
+    };
+    // where the untuned launch splits, the candidates are of the ordinary
+    // form; where it does not, they leave the smaller launches theirs
+    const int split = hop_splits(ctx, prec, layout, a, untuned) ? 0 : untuned.split;
     for (int waves = 1; waves <= 4; ++waves) {
       const int G = waves * gpw;
       if (G > 32 || G < 1) continue;
       for (int nrb = 1; nrb <= G; ++nrb) {
         if (G % nrb || nrb > nrhs || (nrb > 1 && G / nrb < 2)) continue;
         for (int xcd = 0; xcd < 2; ++xcd)
-          for (int pad : {0, 24 * 1024, 44 * 1024}) {
-            HopShape s = {64 * waves, nrb, xcd, pad, 0};
-            // warm-up launch; shapes the kernel rejects (LDS) are skipped
-            if (launch_hop(ctx, prec, layout, dagger, a, st, &s) != QDWF_OK) continue;
-            QDWF_HIP(hipEventRecord(e0, st));
-            for (int r = 0; r < reps; ++r) launch_hop(ctx, prec, layout, dagger, a, st, &s);
-            QDWF_HIP(hipEventRecord(e1, st));
-            QDWF_HIP(hipEventSynchronize(e1));
-            float ms = 0;
-            QDWF_HIP(hipEventElapsedTime(&ms, e0, e1));
-            if (ms / reps < best_t) {
-              best_t = ms / reps;
-              best = s;
-            }
-          }
+          for (int pad : {0, 24 * 1024, 44 * 1024})
+            if (int rc = attempt({64 * waves, nrb, xcd, pad, 0, split})) return rc;
       }
     }
     // the t-sweep serves the full operator wherever it applies; keep it when
@@ -280,19 +306,21 @@ int qdwf_tune(qdwf_ctx* ctx, int prec, int layout, int nrhs, void* ws, void* str
     if (sweep_eligible(ctx, prec, layout, a)) {
       HopShape s = best;
       s.sweep = 1;
-      if (launch_hop(ctx, prec, layout, dagger, a, st, &s) == QDWF_OK) {
-        QDWF_HIP(hipEventRecord(e0, st));
-        for (int r = 0; r < reps; ++r) launch_hop(ctx, prec, layout, dagger, a, st, &s);
-        QDWF_HIP(hipEventRecord(e1, st));
-        QDWF_HIP(hipEventSynchronize(e1));
-        float ms = 0;
-        QDWF_HIP(hipEventElapsedTime(&ms, e0, e1));
-        if (ms / reps < best_t) {
-          best_t = ms / reps;
-          best = s;
-        }
-      }
+      if (int rc = attempt(s)) return rc;
     }
+    // the best shape against the untuned one, in turn
+    double mine[2] = {1e30, 1e30}, theirs[2] = {1e30, 1e30};
+    for (int k = 0; k < 3; ++k)
+      for (int p = 0; p < 2; ++p) {
+        const HopArgs& h = p ? one : a;
+        if (int rc = timed(h, dagger, untuned, &t)) return rc;
+        theirs[p] = std::min(theirs[p], t);
+        if (int rc = timed(h, dagger, best, &t)) return rc;
+        mine[p] = std::min(mine[p], t);
+      }
+    const bool better = mine[0] + mine[1] < theirs[0] + theirs[1];
+    if (!better) best = untuned;
+    best_t = better ? mine[0] : theirs[0];
     {
       std::lock_guard<std::mutex> lk(g_mu);
       g_tuned[ctx][TuneKey(prec, layout, dagger, nrhs)] = best;

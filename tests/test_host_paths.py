@@ -89,3 +89,72 @@ for L, Ls, prec in (((4, 4, 4, 4), 8, 0), ((4, 4, 4, 4), 16, 0), ((8, 8, 8, 8), 
 
 def test_a_padded_small_launch_takes_a_form_that_fits(run):
     run(PAD)
+
+TUNER = """
+for L, Ls, prec in (((4, 4, 4, 4), 8, 0), ((8, 8, 8, 8), 8, 1), ((8, 8, 8, 8), 16, 2)):
+    ctx, n = context(L, Ls)
+    f, g, ws = buf(n * 8), buf(n * 8), buf(lib.qdwf_workspace_bytes(ctx, q.QDWF_OP_TUNE, prec, 1))
+    mws = buf(lib.qdwf_workspace_bytes(ctx, q.QDWF_OP_MDAGM, prec, 1))
+
+    def launches():
+        stub.stub_clear()
+        for d in (0, 1):
+            assert lib.qdwf_apply_D(ctx, g, f, d, prec, q.QDWF_RIRI, 1, None) == 0
+        assert lib.qdwf_apply_MdagM(ctx, g, f, prec, q.QDWF_RIRI, 1, mws, None) == 0
+        return hops()
+
+    plain = launches()
+    ms = (ctypes.c_double * 2)()
+    assert lib.qdwf_tune(ctx, prec, q.QDWF_RIRI, 1, ws, None, ms) == 0
+    # every launch takes the same time on the stand-in: nothing beats the untuned one
+    tuned = launches()
+    assert tuned == plain, (L, Ls, prec, plain, tuned)
+    lib.qdwf_destroy(ctx)
+    # a context that reads the result from the cache launches the same
+    ctx, n = context(L, Ls)
+    assert launches() == plain
+    lib.qdwf_destroy(ctx)
+"""
+
+
+def test_tuning_keeps_the_untuned_launch_where_nothing_beats_it(run, tmp_path):
+    run(TUNER, QDWF_TUNE_CACHE=str(tmp_path / "tune.jsonl"))
+
+
+OLD_CACHE = """
+L, Ls, prec = (4, 4, 4, 4), 8, 0
+path = os.environ.pop("QDWF_TUNE_CACHE")
+ctx, n = context(L, Ls)
+f, g = buf(n * 8), buf(n * 8)
+
+def launched(ctx):
+    stub.stub_clear()
+    assert lib.qdwf_apply_D(ctx, g, f, 0, prec, q.QDWF_RIRI, 1, None) == 0
+    return hops()
+
+plain = launched(ctx)
+ws = buf(lib.qdwf_workspace_bytes(ctx, q.QDWF_OP_TUNE, prec, 1))
+os.environ["QDWF_TUNE_CACHE"] = path
+assert lib.qdwf_tune(ctx, prec, q.QDWF_RIRI, 1, ws, None, None) == 0
+lib.qdwf_destroy(ctx)
+import json
+line = json.loads(open(path).readline())
+assert line["split"] == 1
+del line["split"]
+line.update(threads=128, nrb=1, xcd=0, lds_pad=0, sweep=0)
+for split, same in ((None, True), (0, False), (1, True)):
+    entry = dict(line) if split is None else dict(line, split=split)
+    entry["ms"] = entry.pop("ms")
+    open(path, "w").write(json.dumps(entry) + "\\n")
+    ctx, n = context(L, Ls)
+    shape = (ctypes.c_int32 * 4)()
+    assert lib.qdwf_tuned_shape(ctx, prec, q.QDWF_RIRI, 0, 1, shape) == 0
+    assert list(shape) == [128, 1, 0, 0]
+    assert (launched(ctx) == plain) == same, (split, plain)
+    lib.qdwf_destroy(ctx)
+"""
+
+
+def test_cache_lines_with_and_without_the_form(run, tmp_path):
+    run(OLD_CACHE, QDWF_TUNE_CACHE=str(tmp_path / "tune.jsonl"))
+
