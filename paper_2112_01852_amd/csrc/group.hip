@@ -629,21 +629,23 @@ int GroupEngine::launch_round(hipStream_t st) {
     if (err == hipSuccess) err = e;
     return err == hipSuccess;
   };
-  bool started[CLS_COUNT] = {};
+  bool forked = false, started[CLS_COUNT] = {};
   for (int c = lead + 1; c < CLS_COUNT; ++c) {
     if (!present_[c]) continue;
-    if (!started[lead]) (void)ok(hipEventRecord(fork_, st));
-    started[lead] = true;
-    if (ok(err) && ok(hipStreamWaitEvent(aux_[c], fork_, 0)) && ok(hipGraphLaunch(exec_[c], aux_[c])))
-      started[c] = ok(hipEventRecord(join_[c], aux_[c]));
+    if (!forked) (void)ok(hipEventRecord(fork_, st));
+    forked = true;
+    started[c] = ok(err) && ok(hipStreamWaitEvent(aux_[c], fork_, 0)) &&
+                 ok(hipGraphLaunch(exec_[c], aux_[c]));
   }
   if (ok(err)) (void)ok(hipGraphLaunch(exec_[lead], st));
-  // whatever was started is waited for, also after an error
-  for (int c = lead + 1; c < CLS_COUNT; ++c)
-    if (started[c]) {
-      const hipError_t e = hipStreamWaitEvent(st, join_[c], 0);
-      if (err == hipSuccess) err = e;
-    }
+  // whatever was started is waited for, also after an error: by st, or here
+  for (int c = lead + 1; c < CLS_COUNT; ++c) {
+    if (!started[c]) continue;
+    hipError_t e = hipEventRecord(join_[c], aux_[c]);
+    if (e == hipSuccess) e = hipStreamWaitEvent(st, join_[c], 0);
+    if (e != hipSuccess) (void)hipStreamSynchronize(aux_[c]);
+    if (err == hipSuccess) err = e;
+  }
   QDWF_HIP(err);
   return QDWF_OK;
 }

@@ -158,6 +158,7 @@ struct qdwf_pool {
   hipEvent_t ev = nullptr;
   hipStream_t capture = nullptr;
   bool in_flight = false;
+  bool changed = false;                  // the members are not those of the engine's table
   std::vector<char> slot_busy;
   std::map<qdwf::GeoKey, qdwf::GeoEntry> geo;
   std::deque<qdwf::PoolRequest*> queue;
@@ -489,7 +490,6 @@ int qdwf_pool_step(qdwf_pool* pool, void* stream, int* n_active) {
   Dev dg(pool->device);
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   int rc;
-  bool changed = false;
   // 1. the last round: retire what finished in it
   if (pool->in_flight) {
     QDWF_HIP(hipEventSynchronize(pool->ev));
@@ -513,7 +513,7 @@ int qdwf_pool_step(qdwf_pool* pool, void* stream, int* n_active) {
       // the arena room is reused only by work queued after this unpack
       release(pool, r);
       finish(pool, r, rc ? rc : status_code(s.status));
-      changed = true;
+      pool->changed = true;
     }
     pool->active.swap(still);
   }
@@ -531,19 +531,29 @@ int qdwf_pool_step(qdwf_pool* pool, void* stream, int* n_active) {
     }
     pool->active.push_back(r);
     pool->where[r->id] = 1;
-    changed = true;
+    pool->changed = true;
   }
   // 3. one round for every member
-  if (changed) {
+  if (pool->changed) {
     std::vector<GroupMember> ms;
     for (PoolRequest* r : pool->active) ms.push_back(r->m);
     if ((rc = pool->engine->set_members(ms.data(), (int)ms.size(), st))) return rc;
+    pool->changed = false;
   }
   if (!pool->active.empty()) {
-    if ((rc = pool->engine->launch_round(st))) return rc;
-    QDWF_HIP(hipMemcpyAsync(pool->h_states, pool->d_states, sizeof(RhsState) * pool->max_slots,
-                            hipMemcpyDeviceToHost, st));
-    QDWF_HIP(hipEventRecord(pool->ev, st));
+    rc = [&]() -> int {
+      if (int r = pool->engine->launch_round(st)) return r;
+      QDWF_HIP(hipMemcpyAsync(pool->h_states, pool->d_states, sizeof(RhsState) * pool->max_slots,
+                              hipMemcpyDeviceToHost, st));
+      QDWF_HIP(hipEventRecord(pool->ev, st));
+      return QDWF_OK;
+    }();
+    if (rc) {
+      // part of the round may be running: it reads the table, and the next
+      // step or the pool's end would not know to wait for it
+      (void)hipStreamSynchronize(st);
+      return rc;
+    }
     pool->in_flight = true;
   }
   if (n_active) *n_active = (int)pool->active.size();

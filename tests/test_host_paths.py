@@ -158,3 +158,74 @@ for split, same in ((None, True), (0, False), (1, True)):
 def test_cache_lines_with_and_without_the_form(run, tmp_path):
     run(OLD_CACHE, QDWF_TUNE_CACHE=str(tmp_path / "tune.jsonl"))
 
+POOL = """
+name = {name!r}
+prm = q.qdwf_solve_params(system=0, inner_prec=q.QDWF_F16, layout=q.QDWF_RIRI, max_iter=100, tol=1e-10,
+                          delta=0.1, x0_is_guess=0, check_every=8, use_graph=0)
+L = (4, 4, 4, 4)
+
+def submit(pool, Ls):
+    a, n = action(L, Ls), 256 * Ls * 24
+    r = q.qdwf_request(act=a, U=buf(256 * 72 * 8), b=buf(n * 8), x_out=buf(n * 8), params=prm)
+    i = ctypes.c_uint64()
+    assert lib.qdwf_pool_submit(pool, ctypes.byref(r), ctypes.byref(i)) == 0
+
+class Device:
+    # what the host knows to be over, from the calls in order
+    def __init__(self):
+        self.of, self.seen, self.left, self.n = {{}}, {{}}, set(), 0
+
+    def feed(self, lines):
+        for l in lines:
+            w = l.split()
+            if len(w) > 1 and w[1] == "FAILS":
+                continue
+            if w[0] == "hipGraphLaunch":
+                self.n += 1
+                self.of.setdefault(w[2], set()).add(self.n)
+                self.left.add(self.n)
+            elif w[0] == "hipEventRecord":
+                self.seen[w[1]] = set(self.of.get(w[2], ()))
+            elif w[0] == "hipStreamWaitEvent":
+                self.of.setdefault(w[1], set()).update(self.seen.get(w[2], ()))
+            elif w[0] == "hipEventSynchronize":
+                self.left -= self.seen.get(w[1], set())
+            elif w[0] == "hipStreamSynchronize":
+                self.left -= self.of.get(w[1], set())
+            elif w[0] == "hipGraphExecDestroy" or w[0] == "hipMemcpyAsync" and int(w[1]) > 100000:
+                # the graph, or the table and its staging, of a round that may be running
+                assert not self.left, l
+
+n = 1
+while True:
+    need = lib.qdwf_pool_overhead_bytes(4)
+    for Ls in (8, 16, 28):
+        need += lib.qdwf_request_bytes(ctypes.byref(action(L, Ls)), ctypes.byref(prm)) + 4096
+    pool = ctypes.c_void_p()
+    assert lib.qdwf_pool_create(0, buf(need), need, 4, ctypes.byref(prm), ctypes.byref(pool)) == 0
+    for Ls in (16, 28):
+        submit(pool, Ls)
+    D = Device()
+    D.feed(log())
+    stub.stub_fail(name.encode(), n)
+    lib.qdwf_pool_step(pool, None, None)
+    lines = log()
+    D.feed(lines)
+    stub.stub_fail(b"", 0)
+    submit(pool, 8)
+    assert lib.qdwf_pool_step(pool, None, None) == 0
+    D.feed(log())
+    assert D.n >= 2
+    lib.qdwf_pool_destroy(pool)
+    D.feed(log())
+    if not any(" FAILS " in l for l in lines):
+        break
+    n += 1
+print(n, "calls of", name)
+assert n > 1
+"""
+
+
+@pytest.mark.parametrize("name", ["hipEventRecord", "hipStreamWaitEvent", "hipGraphLaunch", "hipMemcpyAsync"])
+def test_a_round_that_fails_half_way_is_waited_for(run, name):
+    run(POOL.format(name=name))
