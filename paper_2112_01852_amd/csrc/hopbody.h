@@ -640,7 +640,7 @@ int make_hopk(const qdwf_ctx* ctx, int prec, const HopArgs& a, const HopShape& s
   k->nw = site_waves(g.Vh, g.Ls);
   k->cg_x = a.cg_x;
   k->cg_p = a.cg_p;
-  k->nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0);
+  k->nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0, a.nrhs);
   if (a.cg && (a.cg > 3 || k->nrb != 1 || !a.epi || a.npar != 1 || !a.cg_site ||
                (a.cg >= 2 && (!a.cg_r || !a.cg_alpha)) || (a.cg == 3 && (!a.cg_x || !a.cg_p))))
     return fail(QDWF_EINVAL, "fused CG step needs a one-parity hop with epilogue and its buffers");

@@ -16,19 +16,26 @@ __device__ inline int xcd_remap(int bid, int nb) {
   return (x < rem) ? x * (per + 1) + k : rem * (per + 1) + (x - rem) * per + k;
 }
 
-// Whether a launch that writes `bytes` stores them non-temporally. What the
-// hop gathers (each input spinor eight times, from blocks some planes apart)
-// is what L2 should hold, and a stored line only takes its room: with
-// non-temporal stores one-launch calls ran 3-13 % faster at every size tried
-// from 16 MB up (us: FP32 D 16^4 x 8 50.7 -> 44.0, D^dag 12^3x24 x 12 44.5 ->
-// 40.1, FP64 D 16^3x32 x 8 187 -> 178, FP32 D_eo 16^4 x 16 x 12 rhs 417 ->
-// 397). An output that the next launch of the same call reads (chained: the
-// stages of M_pc) is better left in the caches until it is too large for
-// them: M_pc^dag M_pc in FP16 at 16^4 x 16 (12 to 50 MB of right-hand sides)
-// 2-5 % slower, at 24^4 x 16 (127 MB) 464 -> 443, in FP64 (510 MB) 1568 ->
-// 1500.
-inline int nt_stores(size_t bytes, bool chained) {
-  return bytes >= ((size_t)(chained ? 64 : 16) << 20) ? 1 : 0;
+// Whether a launch that writes `bytes` for nrhs right-hand sides stores them
+// non-temporally. What the hop gathers (each input spinor eight times, from
+// blocks some planes apart) is what L2 should hold, and a stored line only
+// takes its room (us, plain / non-temporal): FP32 D 16^4 x 8 50.7 / 44.0, D_eo
+// 16^4 x 16 39.6 / 33.2, FP64 D 12^3x16 x 16 80.4 / 79.1; near the line, 16
+// to 28 MB, FP32 D 8x12^3 x 16 19.3 / 18.6, FP64 8^2x12^2 x 16 27.7 / 26.7,
+// FP16 D 12^4 x 16 17.4 / 16.7. (FP64 from 30 to 64 MB is the exception: D
+// 8x12^3 x 16 40.3 / 41.1, 12^4 x 16 61.5 / 62.0.) Below the line there is as
+// little to lose, 8^4 x 16 in FP32 8.8 / 8.5.
+// An output that the next launch of the same call reads (chained: the stages
+// of M_pc) is better left in the caches until it is too large for them.
+// M_pc^dag M_pc: FP16 16^2x24x32 x 16 (72 MB) 263 / 278, 24^3x16 (81) 300 /
+// 303, 16^2x32^2 (96) 367 / 356, 24^4 (121) 474 / 456; FP32 16^3x24 (72) 224 /
+// 228, 16^3x28 (84) 263.7 / 261.0, 16^3x32 (96) 306 / 292; FP64 12^3x28 (71)
+// 282 / 295, 16^3x14 (84) 288 / 286, 16^4 (96) 328 / 320. A batch keeps them
+// a little longer: FP16 16^4 x 16 three right-hand sides (72) 252 / 274, four
+// (96) 346 / 364, five (120) 469 / 448; FP64 12^3x16 two (81) 307 / 321.
+inline int nt_stores(size_t bytes, bool chained, int nrhs) {
+  const size_t mb = chained ? (nrhs > 1 ? 100 : 84) : 16;
+  return bytes >= (mb << 20) ? 1 : 0;
 }
 
 // Link staging stride in LDS (reals per link): 16-byte aligned rows.

@@ -313,7 +313,7 @@ int launch_pack(qdwf_ctx* ctx, void* dst, int prec, int layout, const void* src,
       k.m_wps = div_magic((uint32_t)(g.Ls * 24 * sizeof(S) / 16));
       const long blocks = (long)k.ntile * nhalf * nrhs;
       if (blocks <= 0x7fffffffL) {
-        k.nt = nt_stores((size_t)total * 24 * (unpack ? sizeof(R) : sizeof(S)), true);
+        k.nt = nt_stores((size_t)total * 24 * (unpack ? sizeof(R) : sizeof(S)), true, nrhs);
         const size_t lds = ((size_t)g.Ls << k.ns_log2) * (24 * sizeof(R) + 16);
         if (unpack)
           hipLaunchKernelGGL((pack_tile_kernel<R, S, true>), dim3((unsigned)blocks),

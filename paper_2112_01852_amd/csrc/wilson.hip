@@ -195,7 +195,7 @@ int run_wilson(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st) {
   constexpr int NT = WilsonForm<S>::threads;
   const long nblk = (g.n5h + NT - 1) / NT;
   const long blocks = nblk * a.npar * a.nrhs;
-  k.nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0);
+  k.nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0, a.nrhs);
   k.nblk = (int)nblk;
   if (blocks > 0x7fffffffL) return fail(QDWF_EINVAL, "problem too large for one launch");
   if (k.wl)
