@@ -16,6 +16,26 @@ __device__ inline int xcd_remap(int bid, int nb) {
   return (x < rem) ? x * (per + 1) + k : rem * (per + 1) + (x - rem) * per + k;
 }
 
+// Half field h and block sb of it for block bid of nb = H x (blocks of a half
+// field): with the blocks numbered half field fastest, each XCD gets a
+// contiguous range, as from xcd_remap, and takes it one half field after
+// another.
+__host__ __device__ inline void xcd_apart(int bid, int nb, int H, int* h, int* sb) {
+  const unsigned x = bid & 7, per = (unsigned)nb >> 3, rem = nb & 7, uH = H;
+  const unsigned n = per + (x < rem), base = x * per + (x < rem ? x : rem);
+  const unsigned q = n / uH, more = n - q * uH;   // `more` half fields have q + 1 of the range
+  unsigned l = (unsigned)bid >> 3, t = 0, d = q + 1;
+  if (l >= more * d) {
+    l -= more * d;
+    t = more;
+    d = q;
+  }
+  const unsigned c = l / d, s0 = base / uH;
+  t += c + (base - s0 * uH);   // half field, counted from the range's first site block
+  *sb = (int)(s0 + (l - c * d) + (t >= uH));
+  *h = (int)(t >= uH ? t - uH : t);
+}
+
 // Whether a launch that writes `bytes` for nrhs right-hand sides stores them
 // non-temporally. What the hop gathers (each input spinor eight times, from
 // blocks some planes apart) is what L2 should hold, and a stored line only

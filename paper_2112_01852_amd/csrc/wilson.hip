@@ -94,7 +94,7 @@ template <class S> struct WilsonForm {
   static constexpr int threads = sizeof(S) == 8 ? 64 : 256;
 };
 
-template <class S, int LAYOUT, bool DAG, bool WL>
+template <class S, int LAYOUT, bool DAG, bool WL, bool APART>
 __global__ void __launch_bounds__(WilsonForm<S>::threads)
 __attribute__((amdgpu_waves_per_eu(WilsonForm<S>::waves, WilsonForm<S>::waves)))
 wilson_kernel(WilK k) {
@@ -105,11 +105,22 @@ wilson_kernel(WilK k) {
   // XCD a contiguous range. Both parities of a region then run together and
   // read its links once from memory (before: 382 us, with this order alone
   // 323, FP32 at 32^3 x 64).
-  const int B = xcd_remap(blockIdx.x, gridDim.x);
-  const int p = k.par0 + B % k.npar;
-  const int sb = B / k.npar;
-  const int r = sb / k.nblk;
-  const long j = (long)(sb - r * k.nblk) * blockDim.x + threadIdx.x;
+  // APART (run_wilson): the blocks of an XCD cover a contiguous range of sites
+  // too, but one half field after another.
+  int p, r, sb;
+  if constexpr (APART) {
+    int h;
+    xcd_apart(blockIdx.x, gridDim.x, k.npar * k.nrhs, &h, &sb);
+    p = k.par0 + (k.npar == 2 ? h & 1 : 0);
+    r = k.npar == 2 ? h >> 1 : h;
+  } else {
+    const int B = xcd_remap(blockIdx.x, gridDim.x);
+    p = k.par0 + B % k.npar;
+    sb = B / k.npar;
+    r = sb / k.nblk;
+    sb -= r * k.nblk;
+  }
+  const long j = (long)sb * blockDim.x + threadIdx.x;
   if (j >= n5) return;   // no barrier below
   const int q = 1 - p;
   const int i = (int)(j / k.Ls), s = (int)(j - (long)i * k.Ls);
@@ -198,10 +209,30 @@ int run_wilson(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st) {
   k.nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0, a.nrhs);
   k.nblk = (int)nblk;
   if (blocks > 0x7fffffffL) return fail(QDWF_EINVAL, "problem too large for one launch");
-  if (k.wl)
-    hipLaunchKernelGGL((wilson_kernel<S, LAYOUT, DAG, true>), dim3((unsigned)blocks), dim3(NT), 0, st, k);
-  else
-    hipLaunchKernelGGL((wilson_kernel<S, LAYOUT, DAG, false>), dim3((unsigned)blocks), dim3(NT), 0, st, k);
+  // One half field after another (APART) while an XCD still finds in the
+  // caches what half fields share, their links: its neighbouring blocks then
+  // share spinors too. D_h, us, half field fastest / apart: FP32 16^3x32 17.7 /
+  // 16.6, 20^4 24.1 / 22.1, 16^3x48 25.3 / 25.1; FP64 16^3x32 37.6 / 36.5;
+  // batches FP32 16^4 with 2, 4 and 12 right-hand sides 17.6 / 15.2, 30.3 /
+  // 25.6, 82 / 69, of one parity 9.1 / 7.7, 16.3 / 11.7, 43 / 30, FP64 with 12
+  // 190 / 175, FP16 20^4 of one parity with 4 23.6 / 21.8. Past the lines: FP32
+  // 16^2x32^2 33.4 / 33.9, 32^3x64 255 / 328, of one parity 16^3x32 with 4 31.5
+  // / 31.8, 20^4 with 4 37.6 / 39.4. A single 16-bit field does not gain (FP16
+  // 20^4 15.3 / 15.7), and with Ls > 1 the slices share the links already.
+  const long lanes = 2 * g.n5h;   // of one right-hand side, both parities
+  const bool apart = g.Ls == 1 && a.npar * a.nrhs > 1 &&
+                     (a.nrhs == 1 ? sizeof(S) >= 4 && lanes <= 196608
+                                  : lanes <= (sizeof(S) >= 4 ? 98304 : 196608));
+  auto launch = [&](auto kern) {
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NT), 0, st, k);
+  };
+  if (k.wl) {
+    if (apart) launch(wilson_kernel<S, LAYOUT, DAG, true, true>);
+    else launch(wilson_kernel<S, LAYOUT, DAG, true, false>);
+  } else {
+    if (apart) launch(wilson_kernel<S, LAYOUT, DAG, false, true>);
+    else launch(wilson_kernel<S, LAYOUT, DAG, false, false>);
+  }
   QDWF_HIP(hipGetLastError());
   return QDWF_OK;
 }
