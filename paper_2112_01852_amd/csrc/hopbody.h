@@ -595,9 +595,12 @@ inline void minv_steps(int Ls, int* nd, int* md) {
   *md = Ls;
 }
 // Whether the hop takes M_ee^-1 with it at this Ls: the series then costs at
-// most six shifts of the result (Ls = 8: 3, 12: 4, 16: 4, 20: 6, 24: 5), less
-// than writing the hop's result and reading it in a launch of its own. Other
-// Ls (odd factor 7 or more) keep launch_local.
+// most seven shifts of the result (Ls = 8: 3, 12: 4, 16: 4, 20: 6, 24: 5, 32: 5,
+// 40: 7, 48: 6), less than writing the hop's result and reading it in a launch
+// of its own, also where one site leaves lanes of a wavefront idle
+// (M_pc^dag M_pc 8^3x16, us, launch of its own / fused: Ls = 40 FP64 225 / 153,
+// FP32 115 / 84, FP16 96 / 67; Ls = 48 456 / 164, 151 / 86, 124 / 66). Other
+// Ls (odd factor 7 or more, and 64) keep launch_local.
 inline bool minv_fused(int Ls) {
   int nd, md;
   minv_steps(Ls, &nd, &md);
