@@ -127,10 +127,12 @@ __device__ inline void k_dot_body(const SA* __restrict__ a, const SB* __restrict
 // halves); then the groups' sums the same way by one wavefront. One block
 // does both levels (values_total) up to kOneBlock values; beyond, a
 // launch of many blocks leaves the groups' sums (group_sums_part) and the
-// second level reads those: the same bits either way. One block reads 8192
-// values (16^4 x 16) in about the time of the launch it saves, solve of 256
-// iterations 36.5 -> 35.5 ms; at 41472 (24^4 x 16) it takes twice that and
-// the solve is 1 % slower than with two launches.
+// second level reads those: the same bits either way, in qdwf_solve and in
+// the serving pool. One block reads 8192 values (16^4 x 16) in about the time
+// of the launch it saves, solve of 256 iterations 36.5 -> 35.5 ms. Solves in
+// FP16, ms, two launches / one block: 12288 values (16^3x24 x 16) 59.6 / 59.3,
+// 16384 (16^3x32) 94.9 / 94.8, 20000 (20^4) 89.35 / 89.53, 24576 (16^3x48)
+// 201.9 / 202.8, 41472 (24^4) 210.5 / 212.8.
 constexpr int ST = 1024;
 constexpr int kGroup = 1024;             // values of a group
 constexpr long kOneBlock = 16384;

@@ -46,8 +46,8 @@ class GroupEngine {
   // inner / layout: precision and layout every member uses; k: iterations
   // per round. table_mem: group_table_bytes() bytes of device memory (kept
   // for the engine's life); capture: a stream with no work in flight used to
-  // capture the round (not the null stream). Host staging for the table is
-  // allocated here (pinned).
+  // capture the rounds (not the null stream; kept for the engine's life).
+  // Host staging for the table is allocated here (pinned).
   static int create(int device, int inner, int layout, int k, void* table_mem,
                     hipStream_t capture, GroupEngine** out);
   ~GroupEngine();
@@ -65,15 +65,18 @@ class GroupEngine {
 
  private:
   GroupEngine() = default;
-  int capture(hipStream_t cs, int c);
+  int capture(int c, bool sums);
   int device_ = 0, inner_ = 0, layout_ = 0, k_ = 1;
   void* table_ = nullptr;     // device
   void* staging_ = nullptr;   // pinned host copy of the table
-  // per class of members (group.hip): its captured round, how many members
-  // it has, and the stream and event its round runs on beside the first's
+  hipStream_t capture_ = nullptr;
+  // per class of members (group.hip): its captured rounds (for members of
+  // ordinary size; of any size), how many members it has, which round they
+  // need, and the stream and event its round runs on beside the first's
   static constexpr int kClasses = 3;
-  hipGraphExec_t exec_[kClasses] = {};
+  hipGraphExec_t exec_[kClasses][2] = {};
   int present_[kClasses] = {};
+  bool sums_[kClasses] = {};
   hipStream_t aux_[kClasses] = {};
   hipEvent_t join_[kClasses] = {}, fork_ = nullptr;
 };

@@ -19,6 +19,7 @@ constexpr int kHopGrid = 2048;     // blocks of a grouped hop launch (256 thread
 constexpr int kLocalThreads = 128;
 constexpr int kLocalGrid = 1024;
 constexpr int kBlasGrid = 2048;    // blocks of a grouped vector launch (RT threads)
+constexpr int kSumsGrid = 256;     // blocks of a grouped first level of sums (RT threads)
 constexpr int kLsMin = 8, kLsMax = 32;   // Ls a group accepts
 
 // Members come in classes, each advanced by its own chain of launches: the
@@ -41,7 +42,7 @@ struct UnitHdr {
 // A class: members [first, first + n) of the table and their units.
 struct ClassHdr {
   int first, n;
-  UnitHdr blas, hop, loc;
+  UnitHdr blas, hop, loc, sums;   // sums: the members with more than kOneBlock wavefronts
 };
 
 // A member's vectors and scalars as the grouped vector kernels see them.
@@ -51,6 +52,7 @@ struct GReq {
   int NB;                 // reduction blocks
   long nw;                // wavefronts of the half field
   double* site;           // one sum per wavefront, written by the fused hops
+  int sums;               // 1: their groups' sums come in part (g_group_sums)
   int vec_s, vec_r;       // the inner vectors may be walked in aligned words
   int vec_b;              // the FP64 source may be walked in aligned words
   int scale;              // inner vectors kept at unit RMS (inner precision below FP64)
@@ -174,6 +176,17 @@ g_local(const Table* __restrict__ t, int c, int which, int fp64, int want) {
     const GReq& r = t->req[un.first + j];                     \
     const int bx = u - un.start_of(j);
 
+// First level of the sums of the members too large for g_alpha and g_beta
+// alone, whose one block per member reads some 18 bytes a cycle: 25 us each at
+// 32^4 x 16 (131072 wavefronts), 4.7 + 4.6 with this launch before them (one
+// request served 957 -> 945 ms; 24^4 x 16, 41472, 275.5 -> 274.1). Members up
+// to kOneBlock are served by rounds without it.
+__global__ void __launch_bounds__(RT) g_group_sums(const Table* __restrict__ t, int c) {
+  GROUP_LOOP(sums, ST_RUN)
+    group_sums_part(r.site, r.nw, r.part, bx, 0);
+  }
+}
+
 // The fused iteration's alpha and beta from the hops' sums (|M_pc p|^2, then
 // |r|^2) as in the single-context solver, and the p pass (x takes its step
 // in the last hop of M_pc^dag).
@@ -181,7 +194,7 @@ __global__ void __launch_bounds__(ST) g_alpha(const Table* __restrict__ t, int c
   __shared__ double sh[ST];
   for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
     const GReq& r = t->req[t->cls[c].first + j];
-    k_alpha_body(r.site, nullptr, r.nw, r.st, 0, sh);
+    k_alpha_body(r.site, r.sums ? r.part : nullptr, r.nw, r.st, 0, sh);
   }
 }
 
@@ -189,7 +202,7 @@ __global__ void __launch_bounds__(ST) g_beta(const Table* __restrict__ t, int c)
   __shared__ double sh[ST];
   for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
     const GReq& r = t->req[t->cls[c].first + j];
-    k_beta_body(r.site, nullptr, r.nw, r.st, r.delta2, 0, sh);
+    k_beta_body(r.site, r.sums ? r.part : nullptr, r.nw, r.st, r.delta2, 0, sh);
   }
 }
 
@@ -291,9 +304,10 @@ size_t local_lds_max(size_t real_bytes) {
 constexpr int kUpdateEvery = 4;
 
 // The launches of one round of class c: k iterations, with reliable updates
-// offered every kUpdateEvery of them.
+// offered every kUpdateEvery of them. sums: for members of any size; else
+// none has more than kOneBlock wavefronts.
 template <class S, class R, int LAYOUT>
-int record_round(const Table* t, int c, int k, hipStream_t st) {
+int record_round(const Table* t, int c, int k, bool sums, hipStream_t st) {
   typedef typename Store<S>::compute T;
   const size_t lds_s = hop_lds_max(sizeof(T), LinkStride<T>::v);
   const size_t lds_d = hop_lds_max(sizeof(double), LinkStride<double>::v);
@@ -346,8 +360,10 @@ int record_round(const Table* t, int c, int k, hipStream_t st) {
     // one iteration of the running members, its vector steps fused into
     // the last hops of M_pc and M_pc^dag
     mpc(S(), lds_s, loc_s, 0, ST_RUN);
+    if (sums) hipLaunchKernelGGL(g_group_sums, dim3(kSumsGrid), bb, 0, st, t, c);
     hipLaunchKernelGGL(g_alpha, og, dim3(ST), 0, st, t, c);
     mpc_dag(S(), lds_s, loc_s, 0, ST_RUN);
+    if (sums) hipLaunchKernelGGL(g_group_sums, dim3(kSumsGrid), bb, 0, st, t, c);
     hipLaunchKernelGGL(g_beta, og, dim3(ST), 0, st, t, c);
     hipLaunchKernelGGL((g_update_p<S>), bg, bb, 0, st, t, c);
   }
@@ -468,6 +484,7 @@ int GroupEngine::create(int device, int inner, int layout, int k, void* table_me
   e->layout_ = layout;
   e->k_ = k;
   e->table_ = table_mem;
+  e->capture_ = capture;
   if (hipHostMalloc(&e->staging_, sizeof(Table)) != hipSuccess) {
     e->staging_ = nullptr;
     delete e;
@@ -475,7 +492,7 @@ int GroupEngine::create(int device, int inner, int layout, int k, void* table_me
   }
   std::memset(e->staging_, 0, sizeof(Table));
   int rc = QDWF_OK;
-  for (int c = 0; c < CLS_COUNT && !rc; ++c) rc = e->capture(capture, c);
+  for (int c = 0; c < CLS_COUNT && !rc; ++c) rc = e->capture(c, false);
   for (int c = 1; c < CLS_COUNT && !rc; ++c)
     if (hipStreamCreateWithFlags(&e->aux_[c], hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&e->join_[c], hipEventDisableTiming) != hipSuccess)
@@ -490,11 +507,12 @@ int GroupEngine::create(int device, int inner, int layout, int k, void* table_me
   return QDWF_OK;
 }
 
-int GroupEngine::capture(hipStream_t cs, int c) {
+int GroupEngine::capture(int c, bool sums) {
+  const hipStream_t cs = capture_;
   QDWF_HIP(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
   const Table* t = reinterpret_cast<const Table*>(table_);
   int rc = by_types(inner_, layout_, [&](auto stag, auto rtag, auto lay) -> int {
-    return record_round<decltype(stag), decltype(rtag), decltype(lay)::value>(t, c, k_, cs);
+    return record_round<decltype(stag), decltype(rtag), decltype(lay)::value>(t, c, k_, sums, cs);
   });
   hipGraph_t graph = nullptr;
   const hipError_t e = hipStreamEndCapture(cs, &graph);
@@ -503,10 +521,10 @@ int GroupEngine::capture(hipStream_t cs, int c) {
     return rc;
   }
   if (e != hipSuccess) return fail(QDWF_EDEVICE, "capture of the round failed: %s", hipGetErrorString(e));
-  const hipError_t e2 = hipGraphInstantiate(&exec_[c], graph, nullptr, nullptr, 0);
+  const hipError_t e2 = hipGraphInstantiate(&exec_[c][sums], graph, nullptr, nullptr, 0);
   (void)hipGraphDestroy(graph);
   if (e2 != hipSuccess) {
-    exec_[c] = nullptr;
+    exec_[c][sums] = nullptr;
     return fail(QDWF_EDEVICE, "instantiation of the round failed: %s", hipGetErrorString(e2));
   }
   return QDWF_OK;
@@ -514,7 +532,8 @@ int GroupEngine::capture(hipStream_t cs, int c) {
 
 GroupEngine::~GroupEngine() {
   for (int c = 0; c < CLS_COUNT; ++c) {
-    if (exec_[c]) (void)hipGraphExecDestroy(exec_[c]);
+    for (hipGraphExec_t e : exec_[c])
+      if (e) (void)hipGraphExecDestroy(e);
     if (aux_[c]) (void)hipStreamDestroy(aux_[c]);
     if (join_[c]) (void)hipEventDestroy(join_[c]);
   }
@@ -524,6 +543,17 @@ GroupEngine::~GroupEngine() {
 
 int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
   if (n < 0 || n > kGroupMax) return fail(QDWF_EINVAL, "%d members, at most %d", n, kGroupMax);
+  // the round of a class with a large member, captured when it first has one
+  bool sums[kClasses] = {};
+  for (int j = 0; j < n; ++j) {
+    const Geom& g = m[j].ctx->g;
+    if (g.Ls < kLsMin || g.Ls > kLsMax)
+      return fail(QDWF_EINVAL, "grouped solves take %d <= Ls <= %d (got %d)", kLsMin, kLsMax, g.Ls);
+    if (site_waves(g.Vh, g.Ls) > kOneBlock) sums[class_of(g.Ls)] = true;
+  }
+  for (int c = 0; c < CLS_COUNT; ++c)
+    if (sums[c] && !exec_[c][1])
+      if (int rc = capture(c, true)) return rc;
   Table& T = *reinterpret_cast<Table*>(staging_);
   // the table lists the members class by class
   int order[kGroupMax], listed = 0;
@@ -534,7 +564,8 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
       if (class_of(m[j].ctx->g.Ls) == c) order[listed++] = j;
     C.n = listed - C.first;
     present_[c] = C.n;
-    C.blas.start[0] = C.hop.start[0] = C.loc.start[0] = 0;
+    sums_[c] = sums[c];
+    C.blas.start[0] = C.hop.start[0] = C.loc.start[0] = C.sums.start[0] = 0;
   }
   const size_t ps = prec_bytes(inner_);
   const size_t rsz = inner_ == QDWF_F64 ? 8 : 4;
@@ -543,8 +574,6 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     const GroupMember& mj = m[order[j]];
     qdwf_ctx* c = mj.ctx;
     const Geom& g = c->g;
-    if (g.Ls < kLsMin || g.Ls > kLsMax)
-      return fail(QDWF_EINVAL, "grouped solves take %d <= Ls <= %d (got %d)", kLsMin, kLsMax, g.Ls);
     const long n5 = g.n5h * 24;
     const Layout L = solver_layout(n5, 1, inner_);
     char* w = mj.ws;
@@ -553,6 +582,7 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     r.n = n5;
     r.NB = reduce_blocks(n5);
     r.nw = site_waves(g.Vh, g.Ls);
+    r.sums = r.nw > kOneBlock;
     // the wavefronts' sums take the room of Ap, which the fused iteration never stores
     r.site = reinterpret_cast<double*>(w + L.off_ap);
     r.xl = w + L.off_xl;
@@ -592,6 +622,7 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     C.blas.start[i + 1] = C.blas.start[i] + r.NB;
     C.hop.start[i + 1] = C.hop.start[i] + hop_units;
     C.loc.start[i + 1] = C.loc.start[i] + (cl == CLS_LOCAL ? (g.Vh + G - 1) / G : 0);
+    C.sums.start[i + 1] = C.sums.start[i] + (r.sums ? (sum_groups(r.nw) + RT / 64 - 1) / (RT / 64) : 0);
   }
   QDWF_HIP(hipMemcpyAsync(table_, staging_, sizeof(Table), hipMemcpyHostToDevice, st));
   return QDWF_OK;
@@ -635,9 +666,9 @@ int GroupEngine::launch_round(hipStream_t st) {
     if (!forked) (void)ok(hipEventRecord(fork_, st));
     forked = true;
     started[c] = ok(err) && ok(hipStreamWaitEvent(aux_[c], fork_, 0)) &&
-                 ok(hipGraphLaunch(exec_[c], aux_[c]));
+                 ok(hipGraphLaunch(exec_[c][sums_[c]], aux_[c]));
   }
-  if (ok(err)) (void)ok(hipGraphLaunch(exec_[lead], st));
+  if (ok(err)) (void)ok(hipGraphLaunch(exec_[lead][sums_[lead]], st));
   // whatever was started is waited for, also after an error: by st, or here
   for (int c = lead + 1; c < CLS_COUNT; ++c) {
     if (!started[c]) continue;
