@@ -123,10 +123,13 @@ HopShape default_shape(const qdwf_ctx* ctx, int prec, int nrhs) {
   if (waves < 1) waves = 1;
   if (waves > 4) waves = 4;
   sh.threads = 64 * waves;
-  // small launches in blocks of one wavefront, which reach more CUs: FP64
-  // M_pc^dag M_pc 8^4 x 16 44.4 -> 37.4 us, FP64 D 8^4 x 8 13.9 -> 11.7, FP16
-  // M_pc^dag M_pc 12^4 x 16 44.8 -> 43.0; at 24^4 x 16 (41472 wavefronts of a
-  // parity) they are 2 (FP16) to 7 % (FP64) slower
+  // small launches in blocks of one wavefront, which reach more CUs. us, blocks
+  // of four / of one: M_pc^dag M_pc FP64 8^4 x 16 (512 wavefronts of a parity)
+  // 44.4 / 37.4, FP16 12^4 x 16 (2592) 44.7 / 42.6, 12^3x16 (3456) 52.0 / 50.3,
+  // 12^3x24 (5184) 71.7 / 68.4, 16^3x32 (16384) 172.7 / 171.2; FP32 3456 80.1 /
+  // 80.6, 5184 118 / 116, 16384 292 / 298; FP64 2592 130.2 / 130.4, 5184 260 /
+  // 256, 16384 612 / 637. FP64 D is the one with a loss below the line, at Ls =
+  // 16 (3456: 76.6 / 79.1) though not at Ls = 8 (2592: 69.0 / 66.4).
   if ((long)site_waves(ctx->g.Vh, ctx->g.Ls) * nrhs <= kSmallWaves) sh.threads = 64;
   sh.split = 1;
   sh.xcd = 1;
