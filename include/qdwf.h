@@ -285,8 +285,9 @@ int qdwf_dot_noalloc(qdwf_ctx* ctx, double* out, const void* x, const void* y, i
 /* ---- solver ----------------------------------------------------------- */
 /* Solves for nrhs right-hand sides at once: every launch of the solve covers
  * all of them (the hop takes one right-hand side per block unless the tuner
- * chose blocks that share their staged links between several), and a
- * right-hand side that has converged or waits for its reliable update skips
+ * chose blocks that share their staged links between several; the second hop
+ * of M_pc and of M_pc^dag, which sums for the CG step, always takes one, in
+ * the untuned shape where the tuned one shares), and a right-hand side that has converged or waits for its reliable update skips
  * its hops. x, b are FP64 fields in params->layout: odd half fields for
  * QDWF_SYS_NORMAL_PC, full fields for QDWF_SYS_FULL. inner_prec = QDWF_F64
  * runs plain FP64 CG; any other value runs CG with that inner precision and
@@ -301,8 +302,9 @@ int qdwf_solve(qdwf_ctx* ctx, void* x, const void* b, int nrhs, const qdwf_solve
 /* ---- autotuner -------------------------------------------------------- */
 /* Times every launch shape of the hop kernel (threads per block, right-hand
  * sides per block, XCD-aware block order, LDS reservation capping resident
- * blocks per CU) on D and D^dag for (prec, layout, nrhs) and keeps the fastest
- * for this context; later calls of every operator with that precision,
+ * blocks per CU) on D and D^dag for (prec, layout, nrhs), the untuned launch
+ * among them, and keeps the fastest for this context (the untuned one unless
+ * another is faster beside it); later calls of every operator with that precision,
  * layout and nrhs use it. If the environment variable QDWF_TUNE_CACHE names a
  * file, results are appended to it and contexts of the same shape created
  * later pick them up. ws: qdwf_workspace_bytes(ctx, QDWF_OP_TUNE, prec, nrhs)
