@@ -42,7 +42,7 @@ struct UnitHdr {
 // A class: members [first, first + n) of the table and their units.
 struct ClassHdr {
   int first, n;
-  UnitHdr blas, hop, loc, sums;   // sums: the members with more than kOneBlock wavefronts
+  UnitHdr blas, hop, loc;
 };
 
 // A member's vectors and scalars as the grouped vector kernels see them.
@@ -50,9 +50,9 @@ struct GReq {
   RhsState* st;
   long n;                 // reals of a half field
   int NB;                 // reduction blocks
+  int sums;               // 1: the groups' sums of site come in part (g_group_sums)
   long nw;                // wavefronts of the half field
   double* site;           // one sum per wavefront, written by the fused hops
-  int sums;               // 1: their groups' sums come in part (g_group_sums)
   int vec_s, vec_r;       // the inner vectors may be walked in aligned words
   int vec_b;              // the FP64 source may be walked in aligned words
   int scale;              // inner vectors kept at unit RMS (inner precision below FP64)
@@ -85,6 +85,7 @@ struct Table {
   HopK hop_d[4][kGroupMax];   // the same in FP64 (reliable updates)
   GLoc loc_s[2][kGroupMax];   // after stages 1 and 3, inner precision
   GLoc loc_d[2][kGroupMax];
+  UnitHdr sums[CLS_COUNT];    // of g_group_sums: the members with more than kOneBlock wavefronts
 };
 
 // The units of a class as a wavefront walks them: lane i holds the first unit
@@ -167,8 +168,9 @@ g_local(const Table* __restrict__ t, int c, int which, int fp64, int want) {
 }
 
 // Walks the units (kind HDR) of the members of class c whose status is WANT.
-#define GROUP_LOOP(HDR, WANT)                                 \
-  const Units un(t, t->cls[c], t->cls[c].HDR);                \
+#define GROUP_LOOP(HDR, WANT) GROUP_UNITS(t->cls[c].HDR, WANT)
+#define GROUP_UNITS(UNITS, WANT)                              \
+  const Units un(t, t->cls[c], UNITS);                        \
   if (!un.any(WANT)) return;                                  \
   for (int u = blockIdx.x; u < un.total; u += gridDim.x) {    \
     const int j = un.owner(u);                                \
@@ -182,7 +184,7 @@ g_local(const Table* __restrict__ t, int c, int which, int fp64, int want) {
 // request served 957 -> 945 ms; 24^4 x 16, 41472, 275.5 -> 274.1). Members up
 // to kOneBlock are served by rounds without it.
 __global__ void __launch_bounds__(RT) g_group_sums(const Table* __restrict__ t, int c) {
-  GROUP_LOOP(sums, ST_RUN)
+  GROUP_UNITS(t->sums[c], ST_RUN)
     group_sums_part(r.site, r.nw, r.part, bx, 0);
   }
 }
@@ -190,19 +192,22 @@ __global__ void __launch_bounds__(RT) g_group_sums(const Table* __restrict__ t, 
 // The fused iteration's alpha and beta from the hops' sums (|M_pc p|^2, then
 // |r|^2) as in the single-context solver, and the p pass (x takes its step
 // in the last hop of M_pc^dag).
+// SUMS: in rounds with g_group_sums
+template <bool SUMS>
 __global__ void __launch_bounds__(ST) g_alpha(const Table* __restrict__ t, int c) {
   __shared__ double sh[ST];
   for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
     const GReq& r = t->req[t->cls[c].first + j];
-    k_alpha_body(r.site, r.sums ? r.part : nullptr, r.nw, r.st, 0, sh);
+    k_alpha_body(r.site, SUMS && r.sums ? r.part : nullptr, r.nw, r.st, 0, sh);
   }
 }
 
+template <bool SUMS>
 __global__ void __launch_bounds__(ST) g_beta(const Table* __restrict__ t, int c) {
   __shared__ double sh[ST];
   for (int j = blockIdx.x; j < t->cls[c].n; j += gridDim.x) {
     const GReq& r = t->req[t->cls[c].first + j];
-    k_beta_body(r.site, r.sums ? r.part : nullptr, r.nw, r.st, r.delta2, 0, sh);
+    k_beta_body(r.site, SUMS && r.sums ? r.part : nullptr, r.nw, r.st, r.delta2, 0, sh);
   }
 }
 
@@ -361,10 +366,10 @@ int record_round(const Table* t, int c, int k, bool sums, hipStream_t st) {
     // the last hops of M_pc and M_pc^dag
     mpc(S(), lds_s, loc_s, 0, ST_RUN);
     if (sums) hipLaunchKernelGGL(g_group_sums, dim3(kSumsGrid), bb, 0, st, t, c);
-    hipLaunchKernelGGL(g_alpha, og, dim3(ST), 0, st, t, c);
+    hipLaunchKernelGGL(sums ? g_alpha<true> : g_alpha<false>, og, dim3(ST), 0, st, t, c);
     mpc_dag(S(), lds_s, loc_s, 0, ST_RUN);
     if (sums) hipLaunchKernelGGL(g_group_sums, dim3(kSumsGrid), bb, 0, st, t, c);
-    hipLaunchKernelGGL(g_beta, og, dim3(ST), 0, st, t, c);
+    hipLaunchKernelGGL(sums ? g_beta<true> : g_beta<false>, og, dim3(ST), 0, st, t, c);
     hipLaunchKernelGGL((g_update_p<S>), bg, bb, 0, st, t, c);
   }
   QDWF_HIP(hipGetLastError());
@@ -565,7 +570,7 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     C.n = listed - C.first;
     present_[c] = C.n;
     sums_[c] = sums[c];
-    C.blas.start[0] = C.hop.start[0] = C.loc.start[0] = C.sums.start[0] = 0;
+    C.blas.start[0] = C.hop.start[0] = C.loc.start[0] = T.sums[c].start[0] = 0;
   }
   const size_t ps = prec_bytes(inner_);
   const size_t rsz = inner_ == QDWF_F64 ? 8 : 4;
@@ -622,7 +627,8 @@ int GroupEngine::set_members(const GroupMember* m, int n, hipStream_t st) {
     C.blas.start[i + 1] = C.blas.start[i] + r.NB;
     C.hop.start[i + 1] = C.hop.start[i] + hop_units;
     C.loc.start[i + 1] = C.loc.start[i] + (cl == CLS_LOCAL ? (g.Vh + G - 1) / G : 0);
-    C.sums.start[i + 1] = C.sums.start[i] + (r.sums ? (sum_groups(r.nw) + RT / 64 - 1) / (RT / 64) : 0);
+    T.sums[cl].start[i + 1] =
+        T.sums[cl].start[i] + (r.sums ? (sum_groups(r.nw) + RT / 64 - 1) / (RT / 64) : 0);
   }
   QDWF_HIP(hipMemcpyAsync(table_, staging_, sizeof(Table), hipMemcpyHostToDevice, st));
   return QDWF_OK;
@@ -660,20 +666,20 @@ int GroupEngine::launch_round(hipStream_t st) {
     if (err == hipSuccess) err = e;
     return err == hipSuccess;
   };
-  bool forked = false, started[CLS_COUNT] = {};
+  bool forked = false, started[CLS_COUNT] = {}, marked[CLS_COUNT] = {};
   for (int c = lead + 1; c < CLS_COUNT; ++c) {
     if (!present_[c]) continue;
     if (!forked) (void)ok(hipEventRecord(fork_, st));
     forked = true;
     started[c] = ok(err) && ok(hipStreamWaitEvent(aux_[c], fork_, 0)) &&
                  ok(hipGraphLaunch(exec_[c][sums_[c]], aux_[c]));
+    if (started[c]) marked[c] = ok(hipEventRecord(join_[c], aux_[c]));
   }
   if (ok(err)) (void)ok(hipGraphLaunch(exec_[lead][sums_[lead]], st));
   // whatever was started is waited for, also after an error: by st, or here
   for (int c = lead + 1; c < CLS_COUNT; ++c) {
     if (!started[c]) continue;
-    hipError_t e = hipEventRecord(join_[c], aux_[c]);
-    if (e == hipSuccess) e = hipStreamWaitEvent(st, join_[c], 0);
+    const hipError_t e = marked[c] ? hipStreamWaitEvent(st, join_[c], 0) : hipErrorUnknown;
     if (e != hipSuccess) (void)hipStreamSynchronize(aux_[c]);
     if (err == hipSuccess) err = e;
   }
