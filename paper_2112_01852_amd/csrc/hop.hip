@@ -138,12 +138,14 @@ HopShape default_shape(const qdwf_ctx* ctx, int prec, int nrhs) {
   // several right-hand sides of a block (the tuner still tries both)
   sh.nrb = 1;
   sh.lds_pad = 0;
-  // the t-sweep of the full operator: measured faster than the checkerboard
-  // traversal in FP32 with 16- and 32-wide rows (one and two blocks of 8
-  // waves per CU); slower with 24-wide ones (6 waves per CU), in BF16
-  // storage, and in FP16 storage since the checkerboard kernel keeps FP16
-  // neighbours packed (32^4 x 16 D 0.73 against 0.84 ms); the tuner tries
-  // it wherever it applies
+  // the t-sweep of the full operator, in FP32 with 16- and 32-wide rows (one
+  // and two blocks of 8 waves per CU): us, sweep / checkerboard, D 32^4 x 16
+  // 991 / 1064, 16^3x64 259 / 268, 16x24^3 223 / 227. Since the checkerboard
+  // kernel streams its outputs it is the faster one on small lattices (16^4
+  // 65 / 56, 16^3x32 120 / 102, 32x16^3 131 / 104, c = 0 alike), which the tuner
+  // finds. Slower with 24-wide rows (6 waves per CU), in BF16 storage, and in
+  // FP16 storage since the checkerboard kernel keeps FP16 neighbours packed
+  // (32^4 x 16 D 0.73 against 0.84 ms); the tuner tries it wherever it applies
   const int Lx = ctx->g.L[0];
   sh.sweep = (prec == QDWF_F32 && (Lx == 16 || Lx == 32)) ? 1 : 0;
   if (const char* e = std::getenv("QDWF_HOP_LDS_PAD")) sh.lds_pad = std::atoi(e);
