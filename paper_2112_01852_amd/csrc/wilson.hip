@@ -87,19 +87,31 @@ struct WilK {
 // waves per SIMD and two directions ahead (three ahead 256, one wave 282),
 // FP64 733 -> 559 at one wave and two ahead (two waves spill: 693) in blocks
 // of one wavefront (604 in blocks of four), FP16 195 -> 156 at two waves and
-// three ahead (two ahead 165).
-template <class S> struct WilsonForm {
-  static constexpr int waves = sizeof(S) == 8 ? 1 : 2;     // per SIMD
-  static constexpr int ahead = sizeof(S) == 2 ? 3 : 2;     // directions in flight
+// three ahead (two ahead 165). That holds for FP16 on 4D fields (F4) in the
+// interleaved layout. Elsewhere 16-bit storage runs at three waves and one
+// ahead: BF16 unpacks what it prefetched at once and so holds 42 registers a
+// direction, fields with Ls > 1 share a site's links between lanes, and split
+// planes load reals singly (us, compiler's own / two waves, three ahead / this
+// form: BF16 16^3x32 x 8 49.9 / 54.3 / 43.6, 12^4 x 12 13.8 / 15.7 / 14.4, 20^4 x
+// 16 121 / 128 / 99, 4D 32^4 85 / 65 / 57, split planes 24^4 x 8 153 / 174 / 141;
+// FP16 16^3x32 x 8 56.0 / 50.0 / 42.9, split planes 12^3x24 x 7 19.9 / 21.1 /
+// 19.6; FP16 4D 32^4 interleaved 86 / 58.3 / 59.8, hence the exception).
+template <class S, int LAYOUT, bool F4> struct WilsonForm {
+  static constexpr bool narrow = sizeof(S) == 2;
+  static constexpr bool deep = narrow && std::is_same<S, _Float16>::value && LAYOUT == QDWF_RIRI && F4;
+  static constexpr int waves = sizeof(S) == 8 ? 1 : narrow && !deep ? 3 : 2;   // per SIMD
+  static constexpr int ahead = deep ? 3 : narrow ? 1 : 2;                      // directions in flight
   static constexpr int threads = sizeof(S) == 8 ? 64 : 256;
 };
 
-template <class S, int LAYOUT, bool DAG, bool WL, bool APART>
-__global__ void __launch_bounds__(WilsonForm<S>::threads)
-__attribute__((amdgpu_waves_per_eu(WilsonForm<S>::waves, WilsonForm<S>::waves)))
+// F4: 4D field; its links come lane-major where the type has such a copy (WL).
+template <class S, int LAYOUT, bool DAG, bool F4, bool APART>
+__global__ void __launch_bounds__((WilsonForm<S, LAYOUT, F4>::threads))
+__attribute__((amdgpu_waves_per_eu((WilsonForm<S, LAYOUT, F4>::waves), (WilsonForm<S, LAYOUT, F4>::waves))))
 wilson_kernel(WilK k) {
   typedef typename Store<S>::compute T;
-  constexpr int PD = WilsonForm<S>::ahead;
+  constexpr bool WL = F4 && sizeof(S) >= 4;
+  constexpr int PD = WilsonForm<S, LAYOUT, F4>::ahead;
   const long n5 = (long)k.Vh * k.Ls;
   // logical block: parity fastest, then sites, then right-hand sides, each
   // XCD a contiguous range. Both parities of a region then run together and
@@ -167,7 +179,7 @@ wilson_kernel(WilK k) {
     recon_acc<MU, SG, D == 0>(uh, acc);
   };
   fetch(IC<0>());
-  fetch(IC<1>());
+  if constexpr (PD > 1) fetch(IC<1>());
   if constexpr (PD > 2) fetch(IC<2>());
   step(IC<0>()); step(IC<1>()); step(IC<2>()); step(IC<3>());
   step(IC<4>()); step(IC<5>()); step(IC<6>()); step(IC<7>());
@@ -203,7 +215,7 @@ int run_wilson(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st) {
   k.epi = a.epi;
   k.hop_scale = a.hop_scale;
   k.alpha = a.alpha;
-  constexpr int NT = WilsonForm<S>::threads;
+  constexpr int NT = WilsonForm<S, LAYOUT, true>::threads;   // whether 4D or not
   const long nblk = (g.n5h + NT - 1) / NT;
   const long blocks = nblk * a.npar * a.nrhs;
   k.nt = nt_stores((size_t)a.npar * a.nrhs * g.n5h * 24 * sizeof(S), a.chained != 0, a.nrhs);
@@ -226,7 +238,7 @@ int run_wilson(qdwf_ctx* ctx, int prec, const HopArgs& a, hipStream_t st) {
   auto launch = [&](auto kern) {
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(NT), 0, st, k);
   };
-  if (k.wl) {
+  if (sizeof(S) >= 4 ? k.wl != nullptr : g.Ls == 1) {
     if (apart) launch(wilson_kernel<S, LAYOUT, DAG, true, true>);
     else launch(wilson_kernel<S, LAYOUT, DAG, true, false>);
   } else {
