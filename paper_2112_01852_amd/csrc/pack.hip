@@ -313,7 +313,17 @@ int launch_pack(qdwf_ctx* ctx, void* dst, int prec, int layout, const void* src,
       k.m_wps = div_magic((uint32_t)(g.Ls * 24 * sizeof(S) / 16));
       const long blocks = (long)k.ntile * nhalf * nrhs;
       if (blocks <= 0x7fffffffL) {
-        k.nt = nt_stores((size_t)total * 24 * (unpack ? sizeof(R) : sizeof(S)), true, nrhs);
+        // Stored non-temporally from 64 MiB (us, plain / non-temporal: pack FP16
+        // from complex64 16^4 x 16 one parity, three right-hand sides, 76 / 64,
+        // FP32 from complex128 12^3x24 x 12 the same 41 / 35), but a slice of a
+        // complex64 field is 96 bytes: its lines reach memory in parts, the
+        // other parity's sites between them (unpack 16^4 x 16 from FP32 27.2 /
+        // 61.9, from FP16 19.6 / 58.5, three right-hand sides from FP64 191 /
+        // 285). One parity from FP64 is bound by its reads and gains again
+        // (24^4 x 8 137 / 103).
+        const size_t bytes = (size_t)total * 24 * (unpack ? sizeof(R) : sizeof(S));
+        const bool parts = unpack && sizeof(R) == 4 && (nhalf == 2 || sizeof(S) < 8);
+        k.nt = !parts && bytes >= ((size_t)64 << 20);
         const size_t lds = ((size_t)g.Ls << k.ns_log2) * (24 * sizeof(R) + 16);
         if (unpack)
           hipLaunchKernelGGL((pack_tile_kernel<R, S, true>), dim3((unsigned)blocks),
